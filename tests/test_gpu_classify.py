@@ -132,3 +132,22 @@ def test_llama_shape_sampled_layers():
     k = aoh_retrieval_group_count(c["hkv"], c["sparsity"])
     _run_and_check(np.stack([w[0] for w in ws]), np.stack([w[1] for w in ws]), c["d"], k,
                    layers=[0, 9, 20, 31], what="llama31 32 layers")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -40])
+def test_structured_spectra(d, scale):
+    # three query heads (not a multiple of the heads a workgroup of the
+    # eigenvalue kernel holds) on a diagonal W_K: equal eigenvalues with no
+    # off-diagonal entry, a diagonal falling over 2^30, and a dense matrix;
+    # scaled down, the Gram products sit near 2^-160
+    r = np.random.default_rng(11)
+    dm = 192
+    wq = np.zeros((3 * d, dm))
+    wk = np.zeros((d, dm))
+    wk[:, :d] = np.eye(d)
+    wq[:d, :d] = np.eye(d)
+    wq[d:2 * d, :d] = np.diag(2.0 ** -np.floor(np.arange(d) * 30 / d))
+    wq[2 * d:] = r.standard_normal((d, dm))
+    hr, _, _ = _run_and_check(scale * wq[None], scale * wk[None], d, 1, what=f"structured {d, scale}")
+    assert abs(hr[0, 0] / d - 1) < 1e-12  # a flat spectrum: its rank
