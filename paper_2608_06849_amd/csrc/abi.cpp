@@ -669,19 +669,40 @@ static aoh_status decode_impl(const aoh_tensor* q, const aoh_paged_cache* kv_ful
     return ok();
   }
 
-  // Plain, anchor and fused steps of up to kWsMaxBatch sequences split the
-  // step's work space on the device (two workgroups per CU), which follows any
-  // mix of lengths and of cache types; larger batches and the reuse layer take
-  // fixed splits from the cache capacity.
+  // Plain, anchor and fused steps split the step's work space on the device
+  // (two workgroups per CU), which follows any mix of lengths and of cache
+  // types.  Many items, or more sequences than the other takes, go to the kernel
+  // that holds whole items, else it is the one whose plan is in registers.
+  // 128 items of d_head 128, 256 of 64, are where the first is never slower (us
+  // a call, first / second): 128 items of 200-2000 tokens 23.3 / 26.9, of
+  // 2K-32K 108.1 / 108.8, 64 items of 4000 tokens 27.8 / 26.0; d_head 64: 128
+  // items of 2K-32K 59.6 / 57.0, 192 of 2K-16K 51.7 / 52.2, 256 of 200-8000
+  // 38.4 / 42.9.  Larger batches, many sequences of a page or two (whose fixed
+  // splits are one workgroup an item and whose workspace is too small) and the
+  // reuse layer take fixed splits from the capacity.
   const int64_t ws_blocks = std::max<int64_t>(max_pages, sp.ring_blocks);
-  if (x.mode != kReuse && B <= kWsMaxBatch && B * Hkv * ws_blocks < (1ll << 30))
-    a.ws_cu = std::min(compute_units(), kWsMaxWgs / 2);
+  const int cu = std::min(compute_units(), kWsMaxWgs / 2);
+  size_t part_rows = (size_t)B * Hq * sp_bound.max_splits;
+  if (x.mode != kReuse) {
+    const size_t many_rows = (size_t)4 * cu * gs;
+    if ((B > kWsMaxBatch || B * Hkv * D >= 128 * 128) && B <= kManyMaxBatch && B * Hkv * (ws_blocks + 16) < (1ll << 29) &&
+        many_rows * (D + 2) * sizeof(float) + 16 + 8 * cu * sizeof(int32_t) <= base_need) {
+      a.many_wgs = 2 * cu;
+      a.ws_cu = cu;
+      part_rows = many_rows;
+      a.out = out->data; a.o_sb = out->stride[0]; a.o_sh = out->stride[1];
+      a.out_f32 = out->dtype == AOH_F32;
+    } else if (B <= kWsMaxBatch && B * Hkv * ws_blocks < (1ll << 30)) {
+      a.ws_cu = cu;
+      part_rows = (size_t)(2 * cu + B * Hkv) * gs;
+    }
+  }
   float* part_acc = reinterpret_cast<float*>(workspace);
-  const size_t acc_floats = a.ws_cu ? (size_t)(2 * a.ws_cu + B * Hkv) * gs * D
-                                    : (size_t)B * Hq * sp_bound.max_splits * D;
-  float* part_ml = part_acc + acc_floats;
+  float* part_ml = part_acc + part_rows * D;
   a.part_acc = part_acc; a.part_ml = part_ml; a.max_splits = sp_bound.max_splits;
-  if (a.ws_cu) a.ws_items = reinterpret_cast<int32_t*>(part_ml + acc_floats / D * 2);
+  if (a.ws_cu) a.ws_items = reinterpret_cast<int32_t*>(part_ml + part_rows * 2);
+  // entries of four int32 are read as 16-byte vectors
+  if (a.many_wgs) a.ws_items = reinterpret_cast<int32_t*>(((uintptr_t)a.ws_items + 15) & ~(uintptr_t)15);
   uint16_t* codes = nullptr;
   float* refs = nullptr;
   uint32_t* keys = nullptr;
@@ -704,6 +725,7 @@ static aoh_status decode_impl(const aoh_tensor* q, const aoh_paged_cache* kv_ful
     a.score_codes = codes;
     a.score_refs = refs;
     a.score_len = max_pages * kPageTokens;
+    a.ml_out = ml;
   }
   if (x.mode == kReuse) {
     a.sel = x.sel_in; a.n_sel = x.top_k; a.n_lists = x.n_lists;
@@ -724,6 +746,7 @@ static aoh_status decode_impl(const aoh_tensor* q, const aoh_paged_cache* kv_ful
   // reuse: a retrieval head's "length" is its number of borrowed entries
   m.max_len = x.mode == kReuse ? x.top_k : max_pages * kPageTokens;
   m.ring_cap = ring_cap;
+  m.many_wgs = a.many_wgs;
   m.ws_cu = a.ws_cu; m.ws_n_ret = hs.n_ret; m.ws_n_str = hs.n_str; m.ws_items = a.ws_items;
   m.streaming_mask = hs.streaming_mask;
   m.ml_out = ml;

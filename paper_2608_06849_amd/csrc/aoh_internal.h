@@ -88,6 +88,16 @@ struct DecodeArgs {
   // and ws_items [B * Hkv][2] each item's first partial slot and count.
   int32_t ws_cu;
   int32_t* ws_items;
+  // > 0: decode_many_kernel with that many workgroups, ws_cu of them in the
+  // first round; 2 * many_wgs slots, ws_items [many_wgs][4] (by workgroup, the
+  // item that starts in it and goes on: partials, sequence, first query head,
+  // ring).  It stores the outputs and, anchor layer, the final (m, l)
+  // [B][Hq][2] of the items that one workgroup holds.
+  int32_t many_wgs;
+  void* out;
+  int64_t o_sb, o_sh;
+  int32_t out_f32;
+  float* ml_out;
   float scale_log2;
   float scale;
   CacheView full;
@@ -134,6 +144,7 @@ struct MergeArgs {
   // ws_n_ret paged KV heads and ws_n_str rings, located through ws_items.
   int32_t ws_cu, ws_n_ret, ws_n_str;
   const int32_t* ws_items;
+  int32_t many_wgs;             // > 0: partials of decode_many_kernel
   uint64_t streaming_mask;      // bit g set = KV head g streaming
   float* ml_out;                // anchor layer: final (m, l) of each paged-cache head, [B][Hq][2]
 };
@@ -248,6 +259,9 @@ constexpr int kRingTargetWaves = 4096;
 // that many partials per item for the merge pass.
 constexpr int kWsMaxBatch = 64;
 constexpr int kWsMaxWgs = 512;
+// Split pass for many items: steps of up to kManyMaxBatch sequences (four a
+// thread in its tables).
+constexpr int kManyMaxBatch = 1024;
 
 // Query rows per bf16 prefill workgroup, and 32-row MFMA blocks per wave
 // (the workgroup has kPrefillRows / (32 * kPrefillRB) waves).

@@ -478,8 +478,8 @@ __device__ __forceinline__ void merge_waves_store(const DecodeArgs& a, f32x4 (&a
   }
 }
 
-// Fixed splits from the cache capacity (batches over kWsMaxBatch sequences,
-// and the reuse layer).  One launch for both cache types: paged-cache items
+// Fixed splits from the cache capacity (the reuse layer, and steps that neither
+// work-space kernel takes).  One launch for both cache types: paged-cache items
 // first, ring items last.  MODE 0: plain decode; 1: anchor layer (paged items
 // also keep their scores); 2: reuse layer (paged items attend to borrowed
 // positions only); 3: plain decode that first stores the new token at
@@ -673,6 +673,325 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_ws_kernel(Decod
       a.ws_items[2 * it.idx + 1] = ws_wg_of(it.off + it.len - 1, p) - w + 1;
     }
     g = it.off + s1;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Split pass for steps of many items (up to kManyMaxBatch sequences): the same
+// work space, in which every item is preceded by kItemCost places without a block: what
+// starting a segment costs a wave (its first loads), in blocks, so that ranges
+// of many short items hold fewer blocks.  Each workgroup takes one contiguous
+// range and each of its waves a consecutive quarter of it.  An item that lies
+// within one wave's quarter is finished and stored by that wave; the pieces of
+// an item that several waves share meet in LDS (at most two a wave: the item
+// its quarter starts in and the one it ends in), and those of several
+// workgroups in the workspace, for the merge launch, which finds them through
+// ws_items: by workgroup, the item that starts in it and goes on, if any.
+//
+// The ranges of the two rounds are those of decode_ws_kernel.  For few items
+// that kernel's plan, which every wave holds in registers, starts faster (9.5 us
+// a launch against 12 for one sequence of 4093 tokens).  For many, its barriers
+// and workspace partials at every item cost more, as do fixed splits of the
+// capacity, of which most are empty when lengths differ: 96 sequences of
+// 200-8000 tokens, 8 KV heads of width 128, capacity 8192: 160 us a step here,
+// 333 with fixed splits; 64 of 200-400 tokens: 28 us here, 51 with the other
+// work-space kernel.  Bound: HBM, 5.4-6 TB/s for full ranges.
+constexpr int kItemCost = 4;
+
+struct ManyPlan {
+  int paged_end;        // places of the paged items
+  int total;            // places of all items
+  int n_old, n_young;   // workgroups of the first and second round
+  int r_old, r_young;   // places per range of each round
+  int g_young;          // first place of the second round's ranges
+};
+
+// Lengths and, per cache type, the exclusive prefix sums over the sequences of
+// an item's places (blocks + kItemCost; 0 for an item without blocks).
+struct ManyTables {
+  int len[kManyMaxBatch];
+  int pre[2][kManyMaxBatch + 4];
+  int carry[2][kSplitWaves];
+};
+
+// Fills the tables from the sequence lengths (thread t: sequences 4t .. 4t + 3)
+// and derives the plan.  Ends with a barrier.
+__device__ __forceinline__ ManyPlan many_plan(const DecodeArgs& a, ManyTables& tb) {
+  static_assert(kManyMaxBatch == 4 * kSplitWaves * kWave, "four sequences a thread");
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const bool many = a.B > 4 * kWave;  // uniform: more sequences than one wave takes
+  if (wave == 0 || many) {
+    int n[2][4], sum[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int b = 4 * t + u;
+      const int len = b < a.B ? a.lens[b] : 0;
+      const int l = max(len, 0);
+      const int nb = a.full.n_kv ? (min(l, a.full.max_pages * kPage) + kPage - 1) / kPage : 0;
+      const int nbr = a.ring.n_kv ? (min(l, a.ring_cap) + kPage - 1) / kPage : 0;
+      n[0][u] = nb ? nb + kItemCost : 0;
+      n[1][u] = nbr ? nbr + kItemCost : 0;
+      if (b < a.B) tb.len[b] = len;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) sum[k] += n[k][u];
+    }
+    int inc[2] = {sum[0], sum[1]};
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int y = __shfl_up(inc[k], o, kWave);
+        if (lane >= o) inc[k] += y;
+      }
+    }
+    if (many) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (lane == kWave - 1) tb.carry[k][wave] = inc[k];
+      __syncthreads();
+      for (int w = 0; w < wave; ++w)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) inc[k] += tb.carry[k][w];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      int at = inc[k] - sum[k];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (4 * t + u < a.B) tb.pre[k][4 * t + u] = at;
+        at += n[k][u];
+      }
+      if (4 * t < a.B && 4 * t + 4 >= a.B) tb.pre[k][a.B] = at;
+    }
+  }
+  __syncthreads();
+  ManyPlan p;
+  p.paged_end = a.full.n_kv * __builtin_amdgcn_readfirstlane(tb.pre[0][a.B]);
+  p.total = p.paged_end + a.ring.n_kv * __builtin_amdgcn_readfirstlane(tb.pre[1][a.B]);
+  const int n_wg = min(a.many_wgs, max(1, (p.total + kWsMinBlocks - 1) / kWsMinBlocks));
+  p.n_old = min(n_wg, a.ws_cu);
+  p.n_young = n_wg - p.n_old;
+  const uint32_t weight = 4 * p.n_old + 3 * p.n_young;  // total < 2^29
+  p.r_old = (int)((4 * (uint32_t)p.total + weight - 1) / weight);
+  p.g_young = min(p.total, p.n_old * p.r_old);
+  p.r_young = p.n_young ? (p.total - p.g_young + p.n_young - 1) / p.n_young : 0;
+  return p;
+}
+
+// Workgroup whose range holds place g (g < total).
+__device__ __forceinline__ int many_wg_of(int g, const ManyPlan& p) {
+  return g < p.g_young ? g / p.r_old : p.n_old + (g - p.g_young) / p.r_young;
+}
+
+// The item holding place g of the work space (g < total): its type, sequence,
+// KV head rank, first place and blocks.
+struct ManyItem {
+  bool ring;
+  int b, kvl, off, len;
+};
+
+__device__ __forceinline__ ManyItem many_item(const DecodeArgs& a, int g, const ManyPlan& p, const ManyTables& tb) {
+  const int lane = threadIdx.x & (kWave - 1);
+  ManyItem it;
+  it.ring = g >= p.paged_end;
+  const int base = it.ring ? p.paged_end : 0;
+  const int heads = it.ring ? a.ring.n_kv : a.full.n_kv;
+  const int* pre = tb.pre[it.ring];
+  int b = 0;
+  for (int b0 = 0; b0 < a.B; b0 += kWave) {
+    const int i = min(b0 + lane, a.B - 1);
+    const uint64_t hit = __ballot(g - base >= heads * pre[i] && g - base < heads * pre[i + 1]);
+    if (hit) {
+      b = b0 + (int)__builtin_ctzll(hit);
+      break;
+    }
+  }
+  it.b = __builtin_amdgcn_readfirstlane(b);
+  const int p0 = __builtin_amdgcn_readfirstlane(pre[it.b]);
+  const int places = max(1, __builtin_amdgcn_readfirstlane(pre[it.b + 1]) - p0);
+  it.kvl = (g - base - heads * p0) / places;
+  it.off = base + heads * p0 + it.kvl * places;
+  it.len = places - kItemCost;
+  return it;
+}
+
+// Four output dimensions d .. d + 3 of query head hq.
+__device__ __forceinline__ void store_out4(const DecodeArgs& a, int b, int hq, int d, f32x4 o) {
+  const int64_t at = (int64_t)b * a.o_sb + (int64_t)hq * a.o_sh + d;
+  if (a.out_f32) {
+    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + at) = o;
+  } else {
+    u32x2 w;
+    w[0] = (uint32_t)f32_to_bf16_bits(o[0]) | ((uint32_t)f32_to_bf16_bits(o[1]) << 16);
+    w[1] = (uint32_t)f32_to_bf16_bits(o[2]) | ((uint32_t)f32_to_bf16_bits(o[3]) << 16);
+    *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(a.out) + at) = w;
+  }
+}
+
+__device__ __forceinline__ void store_ml(const DecodeArgs& a, int b, int hq, float m, float l) {
+  a.ml_out[((int64_t)b * a.Hq + hq) * 2 + 0] = m;
+  a.ml_out[((int64_t)b * a.Hq + hq) * 2 + 1] = l;
+}
+
+// Slot of the partial of an item's j-th workgroup, first + j.  A workgroup
+// shares at most two items with others, the one its range starts in (j > 0) and
+// the one it ends in.
+__device__ __forceinline__ int many_slot(int first, int j) { return 2 * (first + j) + (j == 0 ? 1 : 0); }
+
+template <int D, int MODE>
+__global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_many_kernel(DecodeArgs a) {
+  constexpr int kDimBlocks = D / 16;
+  constexpr int kPieces = 2 * kSplitWaves;
+  __shared__ f32x4 s_acc[kPieces][kDimBlocks][kWave];
+  __shared__ float s_m[kPieces][16], s_l[kPieces][16];
+  __shared__ int s_g[kPieces];  // a place of the piece's segment; -1: no piece
+  __shared__ ManyTables tb;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int col = lane & 15, G = lane >> 4;
+  if (threadIdx.x < kPieces) s_g[threadIdx.x] = -1;
+  const ManyPlan p = many_plan(a, tb);
+  const int w = blockIdx.x;
+
+  int g0, g1;
+  if (w < p.n_old) {
+    g0 = min(w * p.r_old, p.g_young);
+    g1 = min(g0 + p.r_old, p.g_young);
+  } else {
+    g0 = min(p.g_young + (w - p.n_old) * p.r_young, p.total);
+    g1 = w < p.n_old + p.n_young ? min(g0 + p.r_young, p.total) : g0;
+  }
+  // the item shared with later workgroups that starts here: number of
+  // workgroups (0: none), sequence, first query head, whether a ring
+  i32x4 starts = {0, 0, 0, 0};
+  const int share = ((g1 - g0 + kSplitWaves - 1) / kSplitWaves + 1) & ~1;  // whole 32-token chunks
+  const int e1 = min(g1, g0 + share * (wave + 1));
+  for (int g = min(g1, g0 + share * wave); g < e1;) {
+    const ManyItem it = many_item(a, g, p, tb);
+    const int v0 = g - it.off, v1 = min(e1 - it.off, it.len + kItemCost);
+    const int s0 = max(0, v0 - kItemCost), s1 = v1 - kItemCost;
+    const int at = g;
+    g = it.off + v1;
+    if (s0 >= s1) continue;
+    const int len = __builtin_amdgcn_readfirstlane(tb.len[it.b]);
+    f32x4 acc[kDimBlocks];
+#pragma unroll
+    for (int nb = 0; nb < kDimBlocks; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    if (it.ring) decode_split_body<D, true, false, MODE == 3>(a, a.ring, it.b, it.kvl, len, s0, s1, acc, m, l);
+    else decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, it.b, it.kvl, len, s0, s1, acc, m, l);
+    if (s0 == 0 && s1 == it.len) {  // the whole item
+      const int hq = (it.ring ? a.ring : a.full).kv_heads[it.kvl] * a.gs + col;
+      if (col < a.gs) {
+        const float inv = 1.f / l;
+#pragma unroll
+        for (int nb = 0; nb < kDimBlocks; ++nb) {
+          f32x4 o;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = acc[nb][i] * inv;
+          store_out4(a, it.b, hq, 16 * nb + 4 * G, o);
+        }
+        if (MODE == 1 && !it.ring && G == 0) store_ml(a, it.b, hq, m, l);
+      }
+    } else {
+      // the wave's last segment unless the item began before its quarter
+      const int piece = 2 * wave + (s0 == 0 ? 1 : 0);
+#pragma unroll
+      for (int nb = 0; nb < kDimBlocks; ++nb) s_acc[piece][nb][lane] = acc[nb];
+      if (G == 0) {
+        s_m[piece][col] = m;
+        s_l[piece][col] = l;
+      }
+      if (lane == 0) s_g[piece] = at;
+    }
+  }
+  __syncthreads();
+
+  // The pieces, item by item.  Each wave combines a share of the dimension
+  // blocks.  All statistics are read at once and the loops over the pieces are
+  // unrolled (as loops with LDS reads in them they took 1.5 us more).
+  int g_q[kPieces];
+  float m_q[kPieces], l_q[kPieces];
+  {
+    const int g_l = s_g[lane & (kPieces - 1)];
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      g_q[q] = __builtin_amdgcn_readlane(g_l, q);
+      m_q[q] = s_m[q][col];
+      l_q[q] = s_l[q][col];
+    }
+  }
+  for (int from = 0;;) {
+    int at = INT32_MAX;
+#pragma unroll
+    for (int q = kPieces - 1; q >= 0; --q)
+      if (g_q[q] >= from) at = g_q[q];
+    if (at == INT32_MAX) break;
+    const ManyItem it = many_item(a, at, p, tb);
+    const int end = it.off + it.len + kItemCost;
+    from = end;
+    float M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q)
+      if (g_q[q] >= at && g_q[q] < end) M = fmaxf(M, m_q[q]);
+    f32x4 o[kDimBlocks / kSplitWaves];
+#pragma unroll
+    for (int k = 0; k < kDimBlocks / kSplitWaves; ++k) o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      if (!(g_q[q] >= at && g_q[q] < end)) continue;  // uniform
+      const float wt = m_q[q] == -INFINITY ? 0.f : fast_exp2(m_q[q] - M);
+      L += wt * l_q[q];
+#pragma unroll
+      for (int k = 0; k < kDimBlocks / kSplitWaves; ++k) {
+        const f32x4 y = s_acc[q][wave * (kDimBlocks / kSplitWaves) + k][lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[k][i] += wt * y[i];
+      }
+    }
+    const int first = many_wg_of(it.off + kItemCost, p);
+    const int ns = many_wg_of(end - 1, p) - first + 1;
+    const int hq0 = (it.ring ? a.ring : a.full).kv_heads[it.kvl] * a.gs;
+    const int d0 = 16 * wave * (kDimBlocks / kSplitWaves) + 4 * G;
+    if (col < a.gs) {
+      const int64_t row = (int64_t)many_slot(first, w - first) * a.gs + col;
+      const float inv = 1.f / L;
+#pragma unroll
+      for (int k = 0; k < kDimBlocks / kSplitWaves; ++k) {
+        if (ns > 1) {
+          *reinterpret_cast<f32x4*>(a.part_acc + row * D + d0 + 16 * k) = o[k];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[k][i] *= inv;
+          store_out4(a, it.b, hq0 + col, d0 + 16 * k, o[k]);
+        }
+      }
+      if (wave == 0 && G == 0) {
+        if (ns > 1) {
+          a.part_ml[row * 2 + 0] = M;
+          a.part_ml[row * 2 + 1] = L;
+        } else if (MODE == 1 && !it.ring) {
+          store_ml(a, it.b, hq0 + col, M, L);
+        }
+      }
+    }
+    if (w == first && ns > 1) starts = i32x4{ns, it.b, hq0, it.ring};
+  }
+  if (threadIdx.x == 0) *reinterpret_cast<i32x4*>(a.ws_items + 4 * w) = starts;
+
+  // Rows without a key are 0 / 0.
+  for (int b = w; b < a.B; b += gridDim.x) {
+    const bool none[2] = {tb.pre[0][b] == tb.pre[0][b + 1], tb.pre[1][b] == tb.pre[1][b + 1]};
+    for (int k = 0; k < 2; ++k) {
+      const CacheView& cv = k ? a.ring : a.full;
+      if (!none[k]) continue;
+      for (int e = threadIdx.x; e < cv.n_kv * a.gs * (D / 4); e += kSplitWaves * kWave) {
+        const int qh = e / (D / 4), hq = cv.kv_heads[qh / a.gs] * a.gs + qh % a.gs;
+        const float nan = __builtin_nanf("");
+        store_out4(a, b, hq, 4 * (e % (D / 4)), f32x4{nan, nan, nan, nan});
+        if (MODE == 1 && k == 0 && e % (D / 4) == 0) store_ml(a, b, hq, -INFINITY, 0.f);
+      }
+    }
   }
 }
 
@@ -886,6 +1205,67 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(MergeArgs a
   }
 }
 
+// Merge of the decode_many_kernel partials, where an item is in
+// two or three of them at most unless its sequence is far longer than the
+// rest: workgroup w takes the item that starts in split workgroup w and goes
+// on, if there is one, four dimensions of a query head a thread, up to 16
+// partials in flight.  (decode_merge_kernel's workgroup per 32 dimensions of
+// every head took 36 us of 329 for 96 sequences of 32 heads.)
+constexpr int kMergeBatch = 16;
+
+template <int D, bool OUT_F32>
+__global__ __launch_bounds__(kSplitWaves * kWave) void decode_merge_many_kernel(MergeArgs a) {
+  const int first = blockIdx.x;
+  const i32x4 item = *reinterpret_cast<const i32x4*>(a.ws_items + 4 * first);
+  const int ns = item[0], b = item[1], hq0 = item[2];
+  const bool ring = item[3] != 0;
+  for (int q = threadIdx.x; q < a.gs * (D / 4) && ns > 0; q += kSplitWaves * kWave) {
+    const int head = q / (D / 4), d = 4 * (q % (D / 4));
+    float M = -INFINITY, L = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < ns; s0 += kMergeBatch) {
+      float m[kMergeBatch], l[kMergeBatch];
+      f32x4 x[kMergeBatch];
+#pragma unroll
+      for (int s = 0; s < kMergeBatch; ++s)
+        if (s0 + s < ns) {
+          const int64_t row = (int64_t)many_slot(first, s0 + s) * a.gs + head;
+          m[s] = a.part_ml[row * 2 + 0];
+          l[s] = a.part_ml[row * 2 + 1];
+          x[s] = *reinterpret_cast<const f32x4*>(a.part_acc + row * D + d);
+        }
+      float mx = M;
+#pragma unroll
+      for (int s = 0; s < kMergeBatch; ++s)
+        if (s0 + s < ns) mx = fmaxf(mx, m[s]);
+      const float keep = M == -INFINITY ? 0.f : fast_exp2(M - mx);
+      L *= keep;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] *= keep;
+#pragma unroll
+      for (int s = 0; s < kMergeBatch; ++s)
+        if (s0 + s < ns) {
+          const float w = m[s] == -INFINITY ? 0.f : fast_exp2(m[s] - mx);
+          L += w * l[s];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] += w * x[s][i];
+        }
+      M = mx;
+    }
+    const int hq = hq0 + head;
+    const int64_t at = (int64_t)b * a.o_sb + (int64_t)hq * a.o_sh + d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (OUT_F32) reinterpret_cast<float*>(a.out)[at + i] = o[i] / L;
+      else reinterpret_cast<uint16_t*>(a.out)[at + i] = f32_to_bf16_bits(o[i] / L);
+    }
+    if (a.ml_out && !ring && d == 0) {
+      a.ml_out[((int64_t)b * a.Hq + hq) * 2 + 0] = M;
+      a.ml_out[((int64_t)b * a.Hq + hq) * 2 + 1] = L;
+    }
+  }
+}
+
 template <int D>
 static void launch_split_d(const DecodeArgs& a, int mode, int grid, hipStream_t s) {
   const dim3 blk(kSplitWaves * kWave);
@@ -903,7 +1283,20 @@ void launch_ws_d(const DecodeArgs& a, int mode, hipStream_t s) {
   else hipLaunchKernelGGL((decode_ws_kernel<D, 0>), grid, blk, 0, s, a);
 }
 
+template <int D>
+void launch_many_d(const DecodeArgs& a, int mode, hipStream_t s) {
+  const dim3 grid(a.many_wgs), blk(kSplitWaves * kWave);
+  if (mode == 1) hipLaunchKernelGGL((decode_many_kernel<D, 1>), grid, blk, 0, s, a);
+  else if (mode == 3) hipLaunchKernelGGL((decode_many_kernel<D, 3>), grid, blk, 0, s, a);
+  else hipLaunchKernelGGL((decode_many_kernel<D, 0>), grid, blk, 0, s, a);
+}
+
 hipError_t launch_decode_split(const DecodeArgs& a, int d, int mode, hipStream_t s) {
+  if (a.many_wgs) {
+    if (d == 64) launch_many_d<64>(a, mode, s);
+    else launch_many_d<128>(a, mode, s);
+    return hipGetLastError();
+  }
   if (a.ws_cu) {
     if (d == 64) launch_ws_d<64>(a, mode, s);
     else launch_ws_d<128>(a, mode, s);
@@ -930,6 +1323,17 @@ void launch_merge_d(const MergeArgs& a, int out_f32, int grid, hipStream_t s) {
 
 hipError_t launch_decode_merge(const MergeArgs& a, int dtype, int out_f32, int d, hipStream_t s) {
   (void)dtype;
+  if (a.many_wgs) {
+    const dim3 grid(a.many_wgs), blk(kSplitWaves * kWave);
+    if (d == 64) {
+      if (out_f32) hipLaunchKernelGGL((decode_merge_many_kernel<64, true>), grid, blk, 0, s, a);
+      else hipLaunchKernelGGL((decode_merge_many_kernel<64, false>), grid, blk, 0, s, a);
+    } else {
+      if (out_f32) hipLaunchKernelGGL((decode_merge_many_kernel<128, true>), grid, blk, 0, s, a);
+      else hipLaunchKernelGGL((decode_merge_many_kernel<128, false>), grid, blk, 0, s, a);
+    }
+    return hipGetLastError();
+  }
   const int grid = a.B * a.Hq * (d / kMergeDims);
   if (d == 64) {
     if (a.ws_cu) launch_merge_d<64, true>(a, out_f32, grid, s);

@@ -1,0 +1,68 @@
+"""Decode steps of many (sequence, KV head) items on the GPU, against the oracle (Sec. 5, Eq. 8).
+
+From 128 items of d_head 128 (256 of 64) on, or 65 sequences, the split pass holds whole items per wavefront or
+workgroup and merges only what crosses workgroups.  The cases put items on both sides of a wavefront's, a workgroup's
+and many workgroups' range, and cover the sequence tables of one wavefront (256) and of four (1024), and the batches
+beyond them, which take fixed splits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_06849_amd import aoh_decode, aoh_decode_step
+from tests.helpers import assert_parity, bits, f64
+from tests.test_gpu_decode import Run
+from tests.test_gpu_decode_step import assert_same_caches, fused_step
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+CASES = [
+    # B, Hq, Hkv, D, mask, n_sink, window, prompt lens
+    (130, 4, 2, 64, [0, 1], 4, 60, [(37 * i) % 150 + 1 for i in range(130)]),
+    (64, 8, 2, 128, [1, 0], 4, 300, [(91 * i) % 700 + 1 for i in range(64)]),       # 128 items of width 128
+    (66, 14, 2, 128, [0, 0], 8, 32, [9000] + [(7 * i) % 40 + 1 for i in range(65)]),  # one item over many workgroups
+    (70, 4, 4, 64, [1, 1, 1, 1], 16, 100, [(29 * i) % 300 + 1 for i in range(70)]),  # rings only
+    (257, 2, 1, 64, [0], 4, 32, [(13 * i) % 60 + 1 for i in range(257)]),            # tables of four wavefronts
+    (1024, 2, 2, 64, [0, 1], 2, 14, [i % 33 + 1 for i in range(1024)]),
+    (1030, 2, 2, 64, [0, 1], 2, 14, [i % 33 + 1 for i in range(1030)]),              # beyond them
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,mask,n_sink,window,prompt", CASES)
+def test_many_items(B, Hq, Hkv, D, mask, n_sink, window, prompt):
+    runs = [Run(B, Hq, Hkv, D, mask, n_sink, window, prompt, 2, torch.bfloat16, seed=B + Hq) for _ in range(2)]
+    for r in runs:
+        r.append_prompts()
+    run, fused = runs
+    for s in range(2):
+        q, out = run.step(s)
+        assert_parity(out, run.expected(q), torch.bfloat16, f"step {s}")
+        _, got = fused_step(fused, s)
+        assert np.array_equal(bits(got), bits(out)), f"step {s}: fused step differs from append + decode"
+        assert_same_caches(run, fused, f"step {s}")
+        out32 = torch.empty((B, Hq, D), dtype=torch.float32, device=DEV)
+        aoh_decode(q, run.full, run.ring, run.mask, run.lens, n_sink, window, out=out32, workspace=run.ws)
+        assert np.array_equal(bits(out32.to(torch.bfloat16)), bits(out)), f"step {s}: fp32 output differs"
+    run.check_caches()
+
+
+def test_sequences_without_tokens():
+    # padding rows of a batch: no keys, so 0 / 0, and nothing else is disturbed
+    B, Hq, Hkv, D = 130, 4, 2, 128
+    run = Run(B, Hq, Hkv, D, [0, 1], 4, 60, [(37 * i) % 150 + 1 for i in range(B)], 1, torch.bfloat16, seed=3)
+    run.append_prompts()
+    q = run.q_steps[0].to(DEV)
+    want = run.expected(q)
+    lens = run.lens.clone()
+    empty = torch.arange(0, B, 3, device=DEV)
+    lens[empty] = torch.where(empty % 2 == 0, 0, -1).to(torch.int32)
+    out = aoh_decode(q, run.full, run.ring, run.mask, lens, 4, 60, workspace=run.ws)
+    torch.cuda.synchronize()
+    keep = np.ones(B, dtype=bool)
+    keep[::3] = False
+    assert np.isnan(f64(out)[~keep]).all()
+    assert_parity(out[torch.from_numpy(keep).to(DEV)], want[keep], torch.bfloat16, "rows with tokens")
+    new = torch.zeros((B, Hkv, D), dtype=torch.bfloat16, device=DEV)
+    before = [bits(c) for c in (run.full.k, run.ring.k)]
+    aoh_decode_step(q, new, new, run.full, run.ring, run.mask, torch.zeros_like(lens), 4, 60, workspace=run.ws)
+    assert all(np.array_equal(bits(c), w) for c, w in zip((run.full.k, run.ring.k), before))
