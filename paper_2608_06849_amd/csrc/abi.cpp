@@ -235,7 +235,7 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
   HeadSchedule hs;
   if ((st = schedule_heads(head_is_streaming, (int)Hkv, &hs))) return st;
   const int gs = (int)(Hq / Hkv);
-  const int rows = dt == AOH_BF16 ? kPrefillRows : kPrefillRowsF32;
+  const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed);
   const int64_t n_qblocks = ceil_div(T, rows);
   if (n_qblocks * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
   if (append) {
@@ -298,18 +298,18 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
       as.n_cache = hs.n_str; as.ring_blocks = (int)ceil_div(kv_ring->capacity, kPageTokens);
     }
   }
-  if (hs.n_ret && hs.n_str && prefill_mixed_preferred(ar, dt, (int)D)) {
+  if (hs.n_ret && hs.n_str && prefill_mixed_preferred(ar, dt, (int)D, rows)) {
     // One launch, retrieval items first: their causal work dominates
     // (O(T^2) vs O(T(n_sink+window))); the streaming items fill the tail.
-    hipError_t e = launch_prefill_mixed(ar, as, out_f32, s);
+    hipError_t e = launch_prefill_mixed(ar, as, out_f32, (int)D, rows, s);
     if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
   } else {
     if (hs.n_ret) {
-      hipError_t e = launch_prefill(ar, dt, out_f32, (int)D, false, s);
+      hipError_t e = launch_prefill(ar, dt, out_f32, (int)D, rows, false, s);
       if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill retrieval launch: %s", hipGetErrorString(e));
     }
     if (hs.n_str) {
-      hipError_t e = launch_prefill(as, dt, out_f32, (int)D, true, s);
+      hipError_t e = launch_prefill(as, dt, out_f32, (int)D, rows, true, s);
       if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill streaming launch: %s", hipGetErrorString(e));
     }
   }

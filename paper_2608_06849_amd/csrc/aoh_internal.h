@@ -12,7 +12,7 @@ constexpr int kMaxKvHeads = 64;
 constexpr int kPageTokens = 16;  // tokens per cache page / ring block
 
 // One prefill launch covers every query head of the KV heads in kv_heads[]
-// (all of one type).  Work item = (batch, query head, 128-row query block).
+// (all of one type).  Work item = (batch, query head, query block).
 struct PrefillArgs {
   const void* q;
   const void* k;
@@ -194,12 +194,15 @@ struct ClassifyArgs {
 };
 
 // Launchers (return the launch status; no synchronisation).
-hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, bool streaming,
+hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, int rows, bool streaming,
                           hipStream_t s);
-// One launch for a layer with both head types (bf16, d_head 128, short
+// Query rows per workgroup for n_rows tokens in `batch` sequences; PrefillArgs::n_qblocks counts blocks of them.
+int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed);
+// One launch for a layer with both head types (bf16; d_head 64, or short
 // retrieval launches; see prefill.hip).
-bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d);
-hipError_t launch_prefill_mixed(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, hipStream_t s);
+bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d, int rows);
+hipError_t launch_prefill_mixed(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, int d, int rows,
+                                hipStream_t s);
 // mode: 0 plain, 1 anchor (also writes scores), 2 reuse (sparse paged items)
 hipError_t launch_decode_split(const DecodeArgs& a, int d, int mode, hipStream_t s);
 hipError_t launch_decode_merge(const MergeArgs& a, int dtype, int out_f32, int d, hipStream_t s);
@@ -263,10 +266,7 @@ constexpr int kWsMaxWgs = 512;
 // thread in its tables).
 constexpr int kManyMaxBatch = 1024;
 
-// Query rows per bf16 prefill workgroup, and 32-row MFMA blocks per wave
-// (the workgroup has kPrefillRows / (32 * kPrefillRB) waves).
-constexpr int kPrefillRB = 1;
-constexpr int kPrefillRows = 256;
+// Query rows per fp32 prefill workgroup.
 constexpr int kPrefillRowsF32 = 64;
 
 // Host layer (abi.cpp) services for entry points defined in other units.

@@ -8,9 +8,9 @@
 // with chunks of K tokens (the cache before a chunk keeps the sink and the
 // window most recent tokens; the chunk sees those and itself).
 //
-// bf16 kernels.  One workgroup = 8 waves = 256 query rows of one query head;
-// each wave owns 32 rows.  Key/value tiles of 64 keys are staged in LDS and
-// shared by the 8 waves.  Per tile and wave:
+// bf16 kernels.  One workgroup = 128 or 256 query rows of one query head; each
+// wave owns 32 rows.  Key/value tiles of 64 keys are staged in LDS and shared by
+// the workgroup's waves.  Per tile and wave:
 //   S^T[64 keys x 32 rows] = K_tile . Q^T        (v_mfma_f32_32x32x16_bf16)
 //   online softmax in fp32, one query row per lane column, so the row max is a
 //   lane-local reduction plus one exchange with the partner lane (lane ^ 32)
@@ -21,13 +21,11 @@
 // Streaming heads iterate only over the sink tiles and the diagonal band of
 // tiles; other tiles are never loaded.  Tiles that are fully visible skip the
 // per-element mask.
-//   prefill_pp_kernel (d_head 128): direct global->LDS tile loads into a
-//     4-stage ring, swizzled LDS rows, two phase-shifted wave groups,
-//     XCD-aware workgroup order (see its own comment).  A layer with both
-//     head types runs as one launch (prefill_pp_mixed_kernel): retrieval
-//     items first, streaming items after them.
-//   prefill_bf16_kernel (d_head 64): register-staged, double-buffered, padded
-//     LDS tiles.
+//   prefill_pp_kernel: direct global->LDS tile loads into rings of LDS tiles,
+//     swizzled LDS rows, two phase-shifted wave groups, XCD-aware workgroup
+//     order (see its own comment).  A layer with both head types runs as one
+//     launch (prefill_pp_mixed_kernel): retrieval items first, streaming items
+//     after them.
 //
 // fp32 kernel: a plain per-row kernel (one thread per query row) kept exact
 // for fp32 inputs; it has no performance role.
@@ -40,31 +38,8 @@
 namespace aoh {
 
 constexpr int kBN = 64;          // keys per tile
-constexpr int kRB = kPrefillRB;                 // 32-row MFMA blocks per wave
-constexpr int kRowsPerWave = 32 * kRB;
-constexpr int kWaves = kPrefillRows / kRowsPerWave;  // waves per workgroup
-
-// 64-key tiles per LDS stage (one barrier per stage).
-constexpr int kStageTiles = 1;
-
-template <int D>
-struct PrefillLds {
-  // Row paddings (bf16 elements): K rows are read 16 bytes per lane down 32
-  // rows; V rows are read by the transpose read as 4 rows x 32 bytes per
-  // 16 lanes.  Each padding spreads its access pattern over distinct banks.
-  static constexpr int kStrideK = D + 8;
-  static constexpr int kStrideV = D + 32;
-  uint16_t k[kBN * kStageTiles][kStrideK];
-  uint16_t v[kBN * kStageTiles][kStrideV];
-};
-
-// Lazy rescaling threshold (log2 units): the running max used for the
-// exponentials is only raised when a row's true max exceeds it by more than
-// this, so P stays below 2^8 and the O rescale is skipped on most tiles.
-constexpr float kRescaleThreshold = 8.0f;
-
-// d_head-128 kernel: largest sum of a lane's 32 exponentials of one tile,
-// taken against the trailing reference max, that is accepted as it is.
+// Largest sum of a lane's 32 exponentials of one tile, taken against the trailing
+// reference max, that is accepted as it is.
 constexpr float kSumHi = 65536.f;
 
 // First non-sink key visible to row i of a streaming head (may be negative).
@@ -72,7 +47,7 @@ __device__ __forceinline__ int lo_of(int i, int chunk, int window) {
   return chunk ? (i / chunk) * chunk - window : i - window + 1;
 }
 
-// Tile visit plan of one query block [i0, i0 + kPrefillRows).
+// Tile visit plan of one query block [i0, i0 + rows).
 struct TilePlan {
   int n_sink_tiles;  // leading sink tiles visited before the band
   int band_first;    // first band tile
@@ -99,425 +74,6 @@ __device__ __forceinline__ TilePlan make_plan(int i0, int rows, int T, int n_sin
     p.n_visit = p.n_sink_tiles + (last_tile - p.band_first + 1);
   }
   return p;
-}
-
-template <int D, bool STREAM, bool OUT_F32, bool APPEND>
-__global__ __launch_bounds__(kWaves * kWave, kRB == 1 ? 2 : 1) void prefill_bf16_kernel(PrefillArgs a) {
-  __shared__ __align__(16) PrefillLds<D> lds[2];
-  constexpr int kChunksPerRow = D / 8;                     // 16-byte chunks per key row
-  constexpr int kChunksPerThread = kBN * kChunksPerRow / (kWaves * kWave);
-  constexpr int kKSteps = D / 16;                          // MFMA k-steps over D
-  constexpr int kMBlocks = D / 32;                         // 32-dim blocks of O^T
-
-  const int n_qh = a.n_kv * a.gs;
-  const int per_block = n_qh * a.B;
-  const int wg = blockIdx.x;
-  // Heaviest query blocks first (longest-processing-time order) for causal work.
-  int qb = a.n_qblocks - 1 - wg / per_block;
-  const int rem = wg % per_block;
-  int qh_local = rem % n_qh;
-  int b = rem / n_qh;
-  if (a.seq_major) {
-    // Packed batch, sequence-major: the workgroups in flight share one or two
-    // sequences' K/V (cache reuse); heaviest block first within a sequence.
-    int unit = wg / n_qh;
-    qh_local = wg % n_qh;
-    b = -1;
-    for (int s2 = 0; s2 < a.B; ++s2) {
-      const int s0 = min(max(a.cu_seqlens[s2], 0), a.total);
-      const int s1 = min(max(a.cu_seqlens[s2 + 1], s0), a.total);
-      const int nb = (min(s1 - s0, a.T) + kPrefillRows - 1) / kPrefillRows;
-      if (unit < nb) {
-        b = s2;
-        qb = nb - 1 - unit;
-        break;
-      }
-      unit -= nb;
-    }
-    if (b < 0) return;  // past the last sequence's blocks
-  }
-  const int g = a.kv_heads[qh_local / a.gs];
-  const int h = g * a.gs + (qh_local % a.gs);
-
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const int lane = tid & 63;
-  const int l32 = lane & 31;
-  const int h2 = lane >> 5;
-  int T = a.T;
-  int64_t tok0 = 0;  // varlen: first row of this sequence in the packed tensors
-  if (a.cu_seqlens) {
-    const int s0 = min(max(a.cu_seqlens[b], 0), a.total);
-    const int s1 = min(max(a.cu_seqlens[b + 1], s0), a.total);
-    T = min(s1 - s0, a.T);
-    tok0 = s0;
-  }
-  const int i0 = qb * kPrefillRows;
-  if (i0 >= T) return;  // query block past this sequence's end (whole workgroup)
-  const int r0 = i0 + wave * kRowsPerWave;      // first row of this wave
-  int my_row[kRB];                              // row of this lane in each 32-row block
-  int my_lo[kRB];                               // its first visible non-sink key (streaming)
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    my_row[rb] = r0 + 32 * rb + l32;
-    my_lo[rb] = lo_of(my_row[rb], a.chunk, a.window);
-  }
-
-  const int64_t qoff = a.cu_seqlens ? tok0 * a.q_st : (int64_t)b * a.q_sb;
-  const int64_t koff = a.cu_seqlens ? tok0 * a.k_st : (int64_t)b * a.k_sb;
-  const int64_t voff = a.cu_seqlens ? tok0 * a.v_st : (int64_t)b * a.v_sb;
-  const int64_t ooff = a.cu_seqlens ? tok0 * a.o_st : (int64_t)b * a.o_sb;
-  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + qoff + (int64_t)h * a.q_sh;
-  const uint16_t* kp = reinterpret_cast<const uint16_t*>(a.k) + koff + (int64_t)g * a.k_sh;
-  const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + voff + (int64_t)g * a.v_sh;
-
-  // Q^T operands: lane holds row my_row[rb], dims 8*h2 + 16*s .. +8.
-  bf16x8 qreg[kRB][kKSteps];
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-    for (int s = 0; s < kKSteps; ++s) {
-      u32x4 x = {0u, 0u, 0u, 0u};
-      if (my_row[rb] < T) x = ld16(qp + (int64_t)my_row[rb] * a.q_st + 8 * h2 + 16 * s);
-      qreg[rb][s] = __builtin_bit_cast(bf16x8, x);
-    }
-
-  f32x16 acc_o[kRB][kMBlocks];
-  float m_run[kRB];  // reference max (log2 units) of this lane's row
-  float l_run[kRB];  // this lane's partial row sum (partner lane has the rest)
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    m_run[rb] = -INFINITY;
-    l_run[rb] = 0.f;
-#pragma unroll
-    for (int mb = 0; mb < kMBlocks; ++mb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc_o[rb][mb][i] = 0.f;
-  }
-
-  const TilePlan plan = make_plan<STREAM>(i0, kPrefillRows, T, a.n_sink, a.window, a.chunk);
-
-  // Cooperative staging of one stage (kStageTiles tiles of 64 keys): global ->
-  // registers -> LDS (double buffered).  Per-thread row/column are fixed, so
-  // the global address of a tile is one scalar offset away.
-  u32x4 kst[kStageTiles][kChunksPerThread], vst[kStageTiles][kChunksPerThread];
-  int st_row[kChunksPerThread], st_col[kChunksPerThread];
-#pragma unroll
-  for (int r = 0; r < kChunksPerThread; ++r) {
-    const int cidx = tid + r * kWaves * kWave;
-    st_row[r] = cidx / kChunksPerRow;
-    st_col[r] = (cidx % kChunksPerRow) * 8;
-  }
-  auto load_tile = [&](int u, int kb) {
-    if (kb + kBN <= T) {
-#pragma unroll
-      for (int r = 0; r < kChunksPerThread; ++r) {
-        kst[u][r] = ld16(kp + (int64_t)(kb + st_row[r]) * a.k_st + st_col[r]);
-        vst[u][r] = ld16(vp + (int64_t)(kb + st_row[r]) * a.v_st + st_col[r]);
-      }
-    } else {
-      // Ragged last tile: rows past T read row T-1 and are zeroed.
-#pragma unroll
-      for (int r = 0; r < kChunksPerThread; ++r) {
-        const int key = kb + st_row[r];
-        const int key_c = min(key, T - 1);
-        const u32x4 kx = ld16(kp + (int64_t)key_c * a.k_st + st_col[r]);
-        const u32x4 vx = ld16(vp + (int64_t)key_c * a.v_st + st_col[r]);
-        const bool in = key < T;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          kst[u][r][e] = in ? kx[e] : 0u;
-          vst[u][r][e] = in ? vx[e] : 0u;
-        }
-      }
-    }
-  };
-  auto load_stage = [&](int stage) {
-#pragma unroll
-    for (int u = 0; u < kStageTiles; ++u) {
-      const int it = stage * kStageTiles + u;
-      if (it < plan.n_visit) load_tile(u, plan.tile(it) * kBN);
-    }
-  };
-  auto store_stage = [&](PrefillLds<D>& buf) {
-#pragma unroll
-    for (int u = 0; u < kStageTiles; ++u)
-#pragma unroll
-      for (int r = 0; r < kChunksPerThread; ++r) {
-        *reinterpret_cast<u32x4*>(&buf.k[kBN * u + st_row[r]][st_col[r]]) = kst[u][r];
-        *reinterpret_cast<u32x4*>(&buf.v[kBN * u + st_row[r]][st_col[r]]) = vst[u][r];
-      }
-  };
-
-  // Fused append: the first query head of each group writes the K/V tiles of
-  // its block's own rows [i0, i0 + rows) into the cache, from the LDS stage
-  // that already holds them, so every position is written exactly once.
-  // Retrieval: paged cache (K token-major, V dimension-major per page; pages
-  // outside the block table are skipped).  Streaming: the ring keeps a
-  // position only if no later prompt position maps to its slot.
-  const bool writer = APPEND && (qh_local % a.gs) == 0;
-  const int crank = qh_local / a.gs;
-  auto write_tile = [&](const PrefillLds<D>& buf, int u, int kb) {
-    constexpr int kCh = D / 8;
-    uint16_t* ck = static_cast<uint16_t*>(a.ck);
-    uint16_t* cv = static_cast<uint16_t*>(a.cv);
-    if (!STREAM) {
-      for (int e = tid; e < kBN * kCh; e += kWaves * kWave) {
-        const int row = e / kCh, col = (e % kCh) * 8;
-        const int p = kb + row;
-        const int lp = p / kPageTokens;
-        if (p >= T || lp >= a.max_pages) continue;
-        const int page = a.block_table[(int64_t)b * a.max_pages + lp];
-        if (page < 0 || page >= a.num_pages) continue;
-        uint16_t* dst = ck + (((int64_t)page * a.n_cache + crank) * kPageTokens + p % kPageTokens) * D + col;
-        st16(dst, *reinterpret_cast<const u32x4*>(&buf.k[kBN * u + row][col]));
-      }
-      for (int e = tid; e < (kBN / kPageTokens) * D * 2; e += kWaves * kWave) {
-        const int pg = e / (2 * D), d = (e / 2) % D, hf = e % 2;
-        const int p0 = kb + kPageTokens * pg + 8 * hf;
-        const int lp = p0 / kPageTokens;
-        if (p0 >= T || lp >= a.max_pages) continue;
-        const int page = a.block_table[(int64_t)b * a.max_pages + lp];
-        if (page < 0 || page >= a.num_pages) continue;
-        uint16_t* dst = cv + (((int64_t)page * a.n_cache + crank) * D + d) * kPageTokens + 8 * hf;
-        const int row0 = kBN * u + kPageTokens * pg + 8 * hf;
-        if (p0 + 8 <= T) {
-          u32x4 w;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            w[j] = (uint32_t)buf.v[row0 + 2 * j][d] | ((uint32_t)buf.v[row0 + 2 * j + 1][d] << 16);
-          st16(dst, w);
-        } else {
-          for (int j = 0; p0 + j < T; ++j) dst[j] = buf.v[row0 + j][d];
-        }
-      }
-    } else {
-      for (int e = tid; e < kBN * kCh; e += kWaves * kWave) {
-        const int row = e / kCh, col = (e % kCh) * 8;
-        const int p = kb + row;
-        if (p >= T || !(p < a.n_sink || p >= T - a.window)) continue;
-        const int slot = p < a.n_sink ? p : a.n_sink + (p - a.n_sink) % a.window;
-        const int64_t unit = ((int64_t)b * a.n_cache + crank) * a.ring_blocks + slot / kPageTokens;
-        const int r = slot % kPageTokens;
-        st16(ck + unit * (kPageTokens * D) + r * D + col, *reinterpret_cast<const u32x4*>(&buf.k[kBN * u + row][col]));
-        uint16_t* rv = cv + unit * (kPageTokens * D);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) rv[(col + j) * kPageTokens + r] = buf.v[kBN * u + row][col + j];
-      }
-    }
-  };
-
-  const float c = a.scale_log2;
-  // Softmax of one 32-key block of S^T for row block rb, in two halves so the
-  // caller can put independent MFMAs between them:
-  //   block_max:  mask, row max, lazy rescale decision (a wave-uniform branch)
-  //   block_exp:  exponentials into the two P^T operands of the block's key steps
-  auto block_max = [&](int rb, f32x16& sb, int key0, auto masked) {
-    constexpr bool MASKED = decltype(masked)::value;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float x = sb[i];
-      if (MASKED) {
-        const int key = key0 + 8 * (i >> 2) + 4 * h2 + (i & 3);
-        bool vis = key <= my_row[rb];
-        if (STREAM) vis = vis && (key < a.n_sink || key >= my_lo[rb]);
-        x = vis ? x : -INFINITY;
-        sb[i] = x;
-      }
-      mx = fmaxf(mx, x);
-    }
-    mx = wave_xor_max(mx, 32) * c;  // log2 units (c > 0 keeps the order)
-    // Raise the reference max only when some row needs it (wave-uniform).
-    if (__any(mx > m_run[rb] + kRescaleThreshold)) {
-      const float m_new = fmaxf(m_run[rb], mx);
-      // 0 when only m_run is -inf; 1 when the row has seen no visible key yet.
-      const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run[rb] - m_new);
-      m_run[rb] = m_new;
-      l_run[rb] *= alpha;
-#pragma unroll
-      for (int mb = 0; mb < kMBlocks; ++mb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc_o[rb][mb][i] *= alpha;
-    }
-  };
-  auto block_exp = [&](int rb, const f32x16& sb, bf16x8& p_lo, bf16x8& p_hi) {
-    const float m_use = (m_run[rb] == -INFINITY) ? 0.f : m_run[rb];
-    float psum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float p = fast_exp2(fmaf(sb[i], c, -m_use));
-      if (i < 8) p_lo[i] = f32_to_bf16(p);
-      else p_hi[i - 8] = f32_to_bf16(p);
-    }
-    // Row sum of the bf16 P actually fed to P.V: one dot2 with (1, 1) per pair.
-    const bf16x2 ones = {(bf16)1.f, (bf16)1.f};
-#define AOH_DOT2_PAIR(v, j) \
-  psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(v, v, j, j + 1), ones, psum, false)
-    AOH_DOT2_PAIR(p_lo, 0);
-    AOH_DOT2_PAIR(p_lo, 2);
-    AOH_DOT2_PAIR(p_lo, 4);
-    AOH_DOT2_PAIR(p_lo, 6);
-    AOH_DOT2_PAIR(p_hi, 0);
-    AOH_DOT2_PAIR(p_hi, 2);
-    AOH_DOT2_PAIR(p_hi, 4);
-    AOH_DOT2_PAIR(p_hi, 6);
-#undef AOH_DOT2_PAIR
-    l_run[rb] += psum;
-  };
-
-  // S^T of one 32-key block for every row block: each K operand read from LDS
-  // feeds kRB MFMAs.
-  auto qk_block = [&](const PrefillLds<D>& buf, int u, int blk, f32x16 (&sb)[kRB]) {
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sb[rb][i] = 0.f;
-#pragma unroll
-    for (int s = 0; s < kKSteps; ++s) {
-      const bf16x8 kop = *reinterpret_cast<const bf16x8*>(&buf.k[kBN * u + 32 * blk + l32][8 * h2 + 16 * s]);
-#pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) sb[rb] = mfma32(kop, qreg[rb][s], sb[rb]);
-    }
-  };
-  // O^T += V^T . P^T for key step t (keys 16t..16t+15 of the tile): the k
-  // index 8*h2 + j maps to key 16t + 4*h2 + j (j < 4) or 16t + 8 + 4*h2 + (j-4).
-  // Each V^T operand (two transpose reads) feeds kRB MFMAs.
-  const int q16 = lane >> 4;        // 16-lane block
-  const int i16 = lane & 15;
-  auto pv_step = [&](const PrefillLds<D>& buf, int u, int t, const bf16x8 (&pop)[kRB]) {
-    const int vrow = kBN * u + 16 * t + 4 * h2 + (i16 >> 2);
-#pragma unroll
-    for (int mb = 0; mb < kMBlocks; ++mb) {
-      const int vcol = 32 * mb + 16 * (q16 & 1) + 4 * (i16 & 3);
-      const i16x4 lo = lds_read_tr16(&buf.v[vrow][vcol]);
-      const i16x4 hi = lds_read_tr16(&buf.v[vrow + 8][vcol]);
-      // Whole-vector concatenation: per-element bf16 insertion of the
-      // transposed halves is avoided on purpose (it was lowered to a
-      // broadcast of the first element by this toolchain).
-      const i16x8 cat = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      const bf16x8 vop = __builtin_bit_cast(bf16x8, cat);
-#pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) acc_o[rb][mb] = mfma32(vop, pop[rb], acc_o[rb][mb]);
-    }
-  };
-
-  // One 64-key tile for this wave.  MASKED selects the per-element mask; full
-  // tiles carry no mask code.  Order: S^T of block 0, its max; then the S^T
-  // MFMAs of block 1 next to the exponentials of block 0 and the P.V MFMAs of
-  // block 0 next to the max of block 1 (same scheduling region, independent
-  // work for the matrix core and the vector ALU); then block 1.
-  // Wave issue priority (s_setprio, inside this wave only): raised while a wave
-  // issues its MFMA clusters so the matrix core is fed first and the other
-  // wave's vector work fills the gaps.
-  auto prio = [&](int p) {
-    if (p) __builtin_amdgcn_s_setprio(1);
-    else __builtin_amdgcn_s_setprio(0);
-  };
-  auto tile_step = [&](const PrefillLds<D>& buf, int u, int kb, auto masked) {
-    f32x16 s0[kRB], s1[kRB];
-    bf16x8 p0[kRB], p1[kRB], p2[kRB], p3[kRB];  // P^T operands of the 4 key steps
-    prio(1);
-    qk_block(buf, u, 0, s0);
-    prio(0);
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) block_max(rb, s0[rb], kb, masked);
-    prio(1);
-    qk_block(buf, u, 1, s1);
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) block_exp(rb, s0[rb], p0[rb], p1[rb]);
-    pv_step(buf, u, 0, p0);
-    pv_step(buf, u, 1, p1);
-    prio(0);
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) block_max(rb, s1[rb], kb + 32, masked);
-#pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) block_exp(rb, s1[rb], p2[rb], p3[rb]);
-    prio(1);
-    pv_step(buf, u, 2, p2);
-    pv_step(buf, u, 3, p3);
-    prio(0);
-  };
-
-  // Double-buffered main loop: one barrier per stage of kStageTiles tiles.
-  // While stage `st` is computed from lds[st & 1], stage st+1 waits in
-  // registers and is written to the other buffer afterwards; stage st+2 is
-  // fetched from global memory.
-  const int n_stage = (plan.n_visit + kStageTiles - 1) / kStageTiles;
-  if (n_stage > 0) {
-    load_stage(0);
-    store_stage(lds[0]);
-    if (n_stage > 1) load_stage(1);
-  }
-  __syncthreads();
-  for (int st = 0; st < n_stage; ++st) {
-    const PrefillLds<D>& buf = lds[st & 1];
-    if (APPEND && writer)
-      for (int u = 0; u < kStageTiles; ++u) {
-        const int it = st * kStageTiles + u;
-        if (it < plan.n_visit) {
-          const int kb = plan.tile(it) * kBN;
-          if (kb >= i0 && kb < i0 + kPrefillRows) write_tile(buf, u, kb);
-        }
-      }
-#pragma unroll
-    for (int u = 0; u < kStageTiles; ++u) {
-      const int it = st * kStageTiles + u;
-      if (it < plan.n_visit) {
-        const int kb = plan.tile(it) * kBN;
-        // Is any element of this wave's rows x 64 keys visible?  Is every element?
-        const bool wave_dead = (kb > r0 + kRowsPerWave - 1) ||
-                               (STREAM && kb >= a.n_sink && kb + kBN - 1 < lo_of(r0, a.chunk, a.window));
-        if (!wave_dead) {
-          const bool need_mask =
-              (kb + kBN - 1 > r0) ||
-              (STREAM && !(kb + kBN - 1 < a.n_sink || kb >= lo_of(r0 + kRowsPerWave - 1, a.chunk, a.window)));
-          if (need_mask) tile_step(buf, u, kb, std::true_type{});
-          else tile_step(buf, u, kb, std::false_type{});
-        }
-      }
-    }
-    if (st + 1 < n_stage) {
-      store_stage(lds[(st + 1) & 1]);
-      if (st + 2 < n_stage) load_stage(st + 2);
-    }
-    __syncthreads();
-  }
-
-  // Epilogue: normalise by the row sum, store.
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    const float l_tot = wave_xor_sum(l_run[rb], 32);
-    const float inv = 1.f / l_tot;
-    if (my_row[rb] >= T) continue;
-    if (OUT_F32) {
-      float* op = reinterpret_cast<float*>(a.out) + ooff + (int64_t)my_row[rb] * a.o_st +
-                  (int64_t)h * a.o_sh;
-#pragma unroll
-      for (int mb = 0; mb < kMBlocks; ++mb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          f32x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = acc_o[rb][mb][4 * q4 + e] * inv;
-          *reinterpret_cast<f32x4*>(op + 32 * mb + 8 * q4 + 4 * h2) = w;
-        }
-    } else {
-      uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + ooff + (int64_t)my_row[rb] * a.o_st +
-                     (int64_t)h * a.o_sh;
-#pragma unroll
-      for (int mb = 0; mb < kMBlocks; ++mb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          u32x2 w;
-          w[0] = (uint32_t)f32_to_bf16_bits(acc_o[rb][mb][4 * q4 + 0] * inv) |
-                 ((uint32_t)f32_to_bf16_bits(acc_o[rb][mb][4 * q4 + 1] * inv) << 16);
-          w[1] = (uint32_t)f32_to_bf16_bits(acc_o[rb][mb][4 * q4 + 2] * inv) |
-                 ((uint32_t)f32_to_bf16_bits(acc_o[rb][mb][4 * q4 + 3] * inv) << 16);
-          *reinterpret_cast<u32x2*>(op + 32 * mb + 8 * q4 + 4 * h2) = w;
-        }
-    }
-  }
 }
 
 // fp32 reference-grade kernel: one thread per query row, keys visited in
@@ -589,27 +145,29 @@ __global__ __launch_bounds__(kPrefillRowsF32) void prefill_f32_kernel(PrefillArg
 }
 
 // ---------------------------------------------------------------------------
-// D = 128 bf16 kernel, phase-shifted wave groups.
+// bf16 kernel, phase-shifted wave groups.
 //
-// Same work item and products as prefill_bf16_kernel (256 query rows of one
-// query head, 32 rows per wave, S^T = K.Q^T and O^T += V^T.P^T on the 32x32x16
-// bf16 MFMA, online softmax in fp32); differences:
+// Work item: 128 or 256 query rows of one query head (PPShape), 32 rows per
+// wave, S^T = K.Q^T and O^T += V^T.P^T on the 32x32x16 bf16 MFMA, online
+// softmax in fp32.
 //  * K/V tiles move global -> LDS with direct loads (global_load_lds_dwordx4),
-//    no register staging, into a K ring and a V ring of four 16 KB tiles
-//    each, issued two tiles ahead of their first use.
-//  * Rows hold 16 chunks of 16 bytes with no padding; chunk c of row r sits
-//    at c ^ (r & 15) for K and c ^ 4 (r & 3) for V, which keeps the K row
-//    reads and the V transpose reads free of bank conflicts.  Every operand
-//    address is one of 12 per-lane base registers plus a constant, and the
-//    tile loop runs four tiles per pass so that each ring slot is a
-//    compile-time constant too: the operand reads take it as an immediate
-//    offset, with no address arithmetic per tile.
+//    no register staging, into a K ring and a V ring of two to four tiles each
+//    (16 KB a tile for d_head 128, 8 KB for 64), issued one or two tiles ahead
+//    of their first use.
+//  * Rows hold D / 8 chunks of 16 bytes with no padding, swizzled (PPTile) so
+//    that the K row reads and the V transpose reads are free of bank
+//    conflicts.  Every operand address is one of D / 16 + D / 32 per-lane base
+//    registers plus a constant, and the tile loop runs several tiles per pass so
+//    that each ring slot is a compile-time constant too: the operand reads take
+//    it as an immediate offset, with no address arithmetic per tile.
 //  * Per tile t a wave runs an MFMA phase (P(t-1).V(t-1) then K(t).Q^T, at
 //    raised wave priority) and a vector phase (mask, exponentials of S(t)
 //    against a trailing reference max, no max pass unless the tile's
-//    exponentials grow too large); waves 0-3 and waves 4-7 (one of each per
-//    SIMD) run one phase apart, with one workgroup barrier per tile (after
-//    the vector phase for waves 0-3, after the MFMA phase for waves 4-7).
+//    exponentials grow too large), with one workgroup barrier per tile.  With
+//    256 rows, waves 0-3 and waves 4-7 (one of each per SIMD) run one phase
+//    apart: the barrier comes after the vector phase for waves 0-3, after the
+//    MFMA phase for waves 4-7.  With 128 rows the waves of different
+//    workgroups on a SIMD interleave their phases.
 //    The loop has a single path (a tile with no visible key for a wave
 //    yields P = 0), so the accumulators never move between registers.
 //  * The fused cache append writes the block's own (diagonal) tiles after
@@ -618,22 +176,49 @@ __global__ __launch_bounds__(kPrefillRowsF32) void prefill_f32_kernel(PrefillArg
 //    block run on the same XCD (one L2); the light items at the end of a
 //    launch are taken from per-XCD work queues, so that faster XCDs take over
 //    part of the slower ones' share.
-constexpr int kPPStages = 4;  // slots of the K and V rings
-constexpr int kPPD = 128;
-constexpr int kPPRows = kPrefillRows;     // query rows per workgroup (8 waves x 32)
-static_assert(kPPRows == 256 && kPrefillRB == 1, "phase-shifted kernel: 8 waves x 32 rows");
-
-// The LDS rings of the d_head-128 kernel: the K tiles of the kPPStages slots,
-// then their V tiles (a slot's offset within a ring fits the 16-bit immediate
-// offset of an LDS read).
-struct PPRing {
-  uint16_t k[kPPStages][kBN * kPPD];
-  uint16_t v[kPPStages][kBN * kPPD];
+// Shape of a workgroup of ROWS query rows, 32 a wave: 8 waves in two phase-
+// shifted groups, or 4 waves and two (d_head 128) or three (64) workgroups a
+// CU, which drift apart by themselves.  Loads run kAhead tiles ahead.  A tile's K is last read
+// in its own MFMA phase, its V in the next one: with loads two tiles ahead K
+// needs two slots and V three.  The slots also hold a block's diagonal tiles
+// for the append after the loop (ROWS / kBN of them).
+template <int D, int ROWS>
+struct PPShape {
+  static constexpr int kThreads = 2 * ROWS;
+  static constexpr bool kPair = ROWS == 256;
+  static constexpr int kAhead = kPair ? 3 : 2;
+  static constexpr int kKSlots = kPair ? 4 : D == 128 ? 2 : 3;
+  static constexpr int kVSlots = kPair ? 4 : 3;
+  // tiles per pass of the loop, a common multiple of the slots
+  static constexpr int kUnroll = kPair ? 4 : D == 128 ? 6 : 3;
+  static constexpr int kWavesPerSimd = D == 64 ? 3 : 2;
+  static constexpr int kLoads = kBN * (D / 8) / kThreads;  // loads per thread and tile, K or V
+  static_assert(ROWS / kBN <= kKSlots, "the ring holds the diagonal tiles");
 };
-constexpr uint32_t kPPTileBytes = kBN * kPPD * 2;  // one K or V tile
-// Element offset of 16-byte chunk c of row r in a stage's K / V tile.
-__device__ __forceinline__ int pp_koff(int r, int c) { return r * kPPD + 8 * (c ^ (r & 15)); }
-__device__ __forceinline__ int pp_voff(int r, int c) { return r * kPPD + 8 * (c ^ (4 * (r & 3))); }
+
+// The LDS rings: the K tiles of the slots, then the V tiles (a slot's offset
+// within a ring fits the 16-bit immediate offset of an LDS read).
+template <int D, int ROWS>
+struct PPRing {
+  uint16_t k[PPShape<D, ROWS>::kKSlots][kBN * D];
+  uint16_t v[PPShape<D, ROWS>::kVSlots][kBN * D];
+};
+
+// Swizzle of a tile's rows: chunk c of row r is stored at c ^ kx(r) in a K
+// tile and c ^ vx(r) in a V tile.  K operands are read 16 bytes a lane down 32
+// rows: 16 consecutive rows take 16 different 16-byte columns of the 64 banks
+// (a row of d_head 64 spans half of them, so two rows share a pattern).  V
+// operands are read as 4 rows x 64 bytes a half wave: the four land in
+// different quarters.
+template <int D>
+struct PPTile {
+  static constexpr int kChunks = D / 8;                     // 16-byte chunks of a row
+  static constexpr uint32_t kBytes = kBN * D * 2;           // one K or V tile
+  static __device__ __forceinline__ int kx(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
+  static __device__ __forceinline__ int vx(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+  static __device__ __forceinline__ int koff(int r, int c) { return r * D + 8 * (c ^ kx(r)); }
+  static __device__ __forceinline__ int voff(int r, int c) { return r * D + 8 * (c ^ vx(r)); }
+};
 
 // Direct global -> LDS load of 16 bytes per lane: lane L's bytes land at
 // lds_row + 16 L (one contiguous 1 KB block per wave).  Issued as inline
@@ -648,11 +233,11 @@ __device__ __forceinline__ void lds_dma16(const void* gptr, const void* lds_row)
 // s_waitcnt immediates (gfx9 encoding: vmcnt [3:0] and [15:14], expcnt [6:4],
 // lgkmcnt [11:8]); a field at its maximum does not wait.
 constexpr int kWaitVm0 = 0x0 | (0x7 << 4) | (0xF << 8);
-constexpr int kWaitVm4 = 0x4 | (0x7 << 4) | (0xF << 8);
+constexpr int wait_vm(int n) { return n | (0x7 << 4) | (0xF << 8); }  // n < 16
 constexpr int kWaitLgkm0 = 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14);
 
 
-// Work item of a workgroup of the d_head-128 kernels: query block qb (rows
+// Work item of a workgroup: query block qb (rows
 // qb * rows ..), local query head qh_local of the launch's KV-head list and
 // sequence b.  Dense batches use the XCD-aware order below; packed batches
 // with sequence-major order walk cu_seqlens.  Returns false when the
@@ -724,10 +309,9 @@ __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int rows, int
 // outside the block table are skipped) or the ring (a position is kept only
 // if no later prompt position maps to its slot).  Threads tid, tid + nthr, ..
 // take the 16-byte chunks of the tile; crank = the KV head's rank in the cache.
-template <bool STREAM>
+template <int D, bool STREAM>
 __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16_t* tk, const uint16_t* tv, int kb,
                                               int b, int crank, int T, int tid, int nthr) {
-  constexpr int D = kPPD;
   constexpr int kCh = D / 8;
   uint16_t* ck = static_cast<uint16_t*>(a.ck);
   uint16_t* cv = static_cast<uint16_t*>(a.cv);
@@ -740,7 +324,7 @@ __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16
       const int page = a.block_table[(int64_t)b * a.max_pages + lp];
       if (page < 0 || page >= a.num_pages) continue;
       uint16_t* dst = ck + (((int64_t)page * a.n_cache + crank) * kPageTokens + p % kPageTokens) * D + 8 * ch;
-      st16(dst, *reinterpret_cast<const u32x4*>(&tk[pp_koff(row, ch)]));
+      st16(dst, *reinterpret_cast<const u32x4*>(&tk[PPTile<D>::koff(row, ch)]));
     }
     for (int e = tid; e < (kBN / kPageTokens) * D * 2; e += nthr) {
       const int pg = e / (2 * D), d = (e / 2) % D, hf = e % 2;
@@ -756,11 +340,11 @@ __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16
         u32x4 w;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          w[j] = (uint32_t)tv[pp_voff(row0 + 2 * j, dc) + de] |
-                 ((uint32_t)tv[pp_voff(row0 + 2 * j + 1, dc) + de] << 16);
+          w[j] = (uint32_t)tv[PPTile<D>::voff(row0 + 2 * j, dc) + de] |
+                 ((uint32_t)tv[PPTile<D>::voff(row0 + 2 * j + 1, dc) + de] << 16);
         st16(dst, w);
       } else {
-        for (int j = 0; p0 + j < T; ++j) dst[j] = tv[pp_voff(row0 + j, dc) + de];
+        for (int j = 0; p0 + j < T; ++j) dst[j] = tv[PPTile<D>::voff(row0 + j, dc) + de];
       }
     }
   } else {
@@ -771,9 +355,9 @@ __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16
       const int slot = p < a.n_sink ? p : a.n_sink + (p - a.n_sink) % a.window;
       const int64_t unit = ((int64_t)b * a.n_cache + crank) * a.ring_blocks + slot / kPageTokens;
       const int r = slot % kPageTokens;
-      st16(ck + unit * (kPageTokens * D) + r * D + 8 * ch, *reinterpret_cast<const u32x4*>(&tk[pp_koff(row, ch)]));
+      st16(ck + unit * (kPageTokens * D) + r * D + 8 * ch, *reinterpret_cast<const u32x4*>(&tk[PPTile<D>::koff(row, ch)]));
       uint16_t* rv = cv + unit * (kPageTokens * D);
-      const int vo = pp_voff(row, ch);
+      const int vo = PPTile<D>::voff(row, ch);
 #pragma unroll
       for (int j = 0; j < 8; ++j) rv[(8 * ch + j) * kPageTokens + r] = tv[vo + j];
     }
@@ -781,15 +365,16 @@ __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16
 }
 
 // One work item (workgroup index wg of its launch's item space) of the
-// d_head-128 kernel; ring = the workgroup's LDS rings.
-template <bool STREAM, bool OUT_F32, bool APPEND>
-__device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PPRing& ring) {
-  constexpr int D = kPPD;
+// kernel; ring = the workgroup's LDS rings.
+template <int D, int ROWS, bool STREAM, bool OUT_F32, bool APPEND>
+__device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PPRing<D, ROWS>& ring) {
+  using Tile = PPTile<D>;
+  using Shape = PPShape<D, ROWS>;
   constexpr int kKSteps = D / 16;
   constexpr int kMBlocks = D / 32;
 
   int qb, qh_local, b;
-  if (!pp_work_item(a, kPPRows, wg, qb, qh_local, b)) return;
+  if (!pp_work_item(a, ROWS, wg, qb, qh_local, b)) return;
   const int g = a.kv_heads[qh_local / a.gs];
   const int h = g * a.gs + (qh_local % a.gs);
 
@@ -809,7 +394,7 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
     tok0 = s0;
   }
   T = __builtin_amdgcn_readfirstlane(T);
-  const int i0 = qb * kPPRows;
+  const int i0 = qb * ROWS;
   if (i0 >= T) return;
   const int r0 = i0 + wave * 32;
   const int my_row = r0 + l32;
@@ -823,51 +408,50 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   const uint16_t* kp = reinterpret_cast<const uint16_t*>(a.k) + koff + (int64_t)g * a.k_sh;
   const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + voff + (int64_t)g * a.v_sh;
 
-  const TilePlan plan = make_plan<STREAM>(i0, kPPRows, T, a.n_sink, a.window, a.chunk);
+  const TilePlan plan = make_plan<STREAM>(i0, ROWS, T, a.n_sink, a.window, a.chunk);
   const int n = __builtin_amdgcn_readfirstlane(plan.n_visit);
   if (n < 1) return;  // a block with rows below T always has its diagonal tile
 
-  // Direct loads of tile `it` into stage it % 4: wave w fills rows 8w .. 8w+7
-  // of K and of V, one 4-row (1 KB) instruction at a time; lane L writes
-  // physical chunk L % 16 of row 4j + L / 16 and therefore fetches the
-  // logical chunk that the swizzle puts there.  Rows past the sequence end
-  // repeat its last row (those keys are masked for every query row).
-  // Per-lane element offsets of the two 4-row blocks this wave loads, relative
-  // to the tile's first key (full tiles), and the rows themselves (the ragged
-  // last tile clamps them).
-  int64_t dma_k[2], dma_v[2];
-  int dma_r[2];
+  // Direct loads of tile `it` into its slots: wave w fills kLoads blocks of
+  // 1 KB (512 / D rows) of K and of V, one instruction each; lane L writes
+  // physical chunk L % kChunks of its row and therefore fetches the logical
+  // chunk that the swizzle puts there.  Rows past the sequence end repeat its
+  // last row (those keys are masked for every query row).  Per-lane element
+  // offsets relative to the tile's first key (full tiles), and the rows
+  // themselves (the ragged last tile clamps them).
+  constexpr int kBlockRows = 512 / D;
+  int64_t dma_k[Shape::kLoads], dma_v[Shape::kLoads];
+  int dma_r[Shape::kLoads];
 #pragma unroll
-  for (int jj = 0; jj < 2; ++jj) {
-    const int j = 2 * wave + jj;
-    const int r = 4 * j + (lane >> 4);
-    const int pc = lane & 15;
+  for (int jj = 0; jj < Shape::kLoads; ++jj) {
+    const int r = kBlockRows * (Shape::kLoads * wave + jj) + lane / Tile::kChunks;
+    const int pc = lane % Tile::kChunks;
     dma_r[jj] = r;
-    dma_k[jj] = (int64_t)r * a.k_st + 8 * (pc ^ (r & 15));
-    dma_v[jj] = (int64_t)r * a.v_st + 8 * (pc ^ (4 * (r & 3)));
+    dma_k[jj] = (int64_t)r * a.k_st + 8 * (pc ^ Tile::kx(r));
+    dma_v[jj] = (int64_t)r * a.v_st + 8 * (pc ^ Tile::vx(r));
   }
   auto issue_tile = [&](int it) {
     const int kb = plan.tile(it) * kBN;
-    uint16_t* sk = ring.k[it % kPPStages];
-    uint16_t* sv = ring.v[it % kPPStages];
+    uint16_t* sk = ring.k[it % Shape::kKSlots];
+    uint16_t* sv = ring.v[it % Shape::kVSlots];
     if (kb + kBN <= T) {
       const uint16_t* kt = kp + (int64_t)kb * a.k_st;
       const uint16_t* vt = vp + (int64_t)kb * a.v_st;
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * wave + jj;
-        lds_dma16(kt + dma_k[jj], &sk[4 * j * kPPD]);
-        lds_dma16(vt + dma_v[jj], &sv[4 * j * kPPD]);
+      for (int jj = 0; jj < Shape::kLoads; ++jj) {
+        const int j = Shape::kLoads * wave + jj;
+        lds_dma16(kt + dma_k[jj], &sk[512 * j]);
+        lds_dma16(vt + dma_v[jj], &sv[512 * j]);
       }
     } else {
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * wave + jj;
+      for (int jj = 0; jj < Shape::kLoads; ++jj) {
+        const int j = Shape::kLoads * wave + jj;
         const int r = dma_r[jj];
-        const int pc = lane & 15;
+        const int pc = lane % Tile::kChunks;
         const int64_t row = min(kb + r, T - 1);
-        lds_dma16(kp + row * a.k_st + 8 * (pc ^ (r & 15)), &sk[4 * j * kPPD]);
-        lds_dma16(vp + row * a.v_st + 8 * (pc ^ (4 * (r & 3))), &sv[4 * j * kPPD]);
+        lds_dma16(kp + row * a.k_st + 8 * (pc ^ Tile::kx(r)), &sk[512 * j]);
+        lds_dma16(vp + row * a.v_st + 8 * (pc ^ Tile::vx(r)), &sv[512 * j]);
       }
     }
   };
@@ -888,17 +472,18 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
 
   // Per-lane LDS byte addresses.  K operand of step s, block blk: row
   // 32 blk + l32, logical chunk 2 s + h2; with the swizzle that is
-  // kaddr0 ^ 32 s (+ 8 KB per block).  V^T operand of key step ks, 32-dim
+  // kaddr0 ^ 32 s (+ 64 D bytes per block).  V^T operand of key step ks, 32-dim
   // block mb (transpose reads): row 16 ks + 4 h2 + i16 / 4 (+ 8 rows for the
   // second half), logical chunk 4 mb + 2 (q16 & 1) + (i16 & 3) / 2, 4 more
-  // elements for odd i16; that is vaddr0 ^ 64 mb (+ 4 KB per key step).
+  // elements for odd i16; that is vaddr0 ^ 64 mb (+ 32 D bytes per key step).
+  // (8, 16 or 32 rows more leave the swizzle as it is.)
   const int q16 = lane >> 4;
   const int i16 = lane & 15;
   const uint32_t kring0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&ring.k[0][0]));
   const uint32_t vring0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&ring.v[0][0]));
-  const uint32_t kaddr0 = 2u * (uint32_t)pp_koff(l32, h2);
+  const uint32_t kaddr0 = 2u * (uint32_t)PPTile<D>::koff(l32, h2);
   const int vrow0 = 4 * h2 + (i16 >> 2);
-  const uint32_t vaddr0 = 2u * (uint32_t)(pp_voff(vrow0, 2 * (q16 & 1) + ((i16 & 3) >> 1)) + 4 * (i16 & 1));
+  const uint32_t vaddr0 = 2u * (uint32_t)(PPTile<D>::voff(vrow0, 2 * (q16 & 1) + ((i16 & 3) >> 1)) + 4 * (i16 & 1));
   // The swizzle XORs touch bits below 256 and the rings are 1 KB aligned, so
   // a slot offset adds after them: operand addresses are these per-lane bases
   // plus constants (immediate offsets once the slot is known at compile time).
@@ -909,13 +494,13 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   for (int mb = 0; mb < kMBlocks; ++mb) vx[mb] = (vring0 + vaddr0) ^ (64u * mb);
   auto k_operand = [&](int st, int s, int blk) {
     typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-    return *reinterpret_cast<lds_bf16x8*>(kx[s] + (uint32_t)st * kPPTileBytes + 8192u * blk);
+    return *reinterpret_cast<lds_bf16x8*>(kx[s] + (uint32_t)st * Tile::kBytes + 64u * D * blk);
   };
   auto v_operand = [&](int st, int ks, int mb) {
     typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-    const uint32_t a = vx[mb] + (uint32_t)st * kPPTileBytes + 4096u * ks;
+    const uint32_t a = vx[mb] + (uint32_t)st * Tile::kBytes + 32u * D * ks;
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(a));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(a + 2048u));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(a + 16u * D));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
@@ -929,16 +514,12 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
 
   // Fused append: the first query head of each group copies its block's own
   // K/V rows from LDS into the cache.  They are the block's diagonal tiles,
-  // the last (up to four) tiles of the loop, which the ring still holds when
+  // the last tiles of the loop, which the ring still holds when
   // the loop ends; the workgroup writes them then.
   const bool writer = APPEND && (qh_local % a.gs) == 0;
   const int crank = qh_local / a.gs;
-  auto write_tile = [&](int st, int kb) {
-    pp_write_tile<STREAM>(a, ring.k[st], ring.v[st], kb, b, crank, T, tid, 512);
-  };
-
-  // MFMA phase of tile t (stage st = t % kPPStages): O^T += V(t-1)^T
-  // P(t-1)^T (stage vst), then S^T(t) = K(t) Q^T.
+  // MFMA phase of tile t (K slot st): O^T += V(t-1)^T P(t-1)^T (V slot vst),
+  // then S^T(t) = K(t) Q^T.
   auto pv_part = [&](int vst) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
@@ -955,11 +536,11 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) sacc[blk] = mfma32(k_operand(st, s, blk), qreg[s], sacc[blk]);
   };
-  auto append_tile = [&](int t, int st) {
-    if (APPEND && writer) {
-      const int kb = plan.tile(t) * kBN;
-      if (kb >= i0 && kb < i0 + kPPRows) write_tile(st, kb);
-    }
+  auto append_tile = [&](int t) {
+    const int kb = plan.tile(t) * kBN;
+    if (kb >= i0 && kb < i0 + ROWS)
+      pp_write_tile<D, STREAM>(a, ring.k[t % Shape::kKSlots], ring.v[t % Shape::kVSlots], kb, b, crank, T, tid,
+                               Shape::kThreads);
   };
   // Steady-state MFMA phase.  Both products run unconditionally (a wave with
   // no visible key in a tile gets P = 0 from its vector phase), so the loop
@@ -967,20 +548,21 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   // The MFMA phase runs at raised wave priority (s_setprio, this wave only):
   // its SIMD also holds a wave of the other group in its vector phase, and
   // the matrix core is kept fed first (2-3% faster than equal priority).
-  auto mfma_phase = [&](int t, int st) {
+  auto mfma_phase = [&](int st, int vst) {
     __builtin_amdgcn_s_setprio(1);
-    pv_part((st + kPPStages - 1) % kPPStages);
+    pv_part(vst);
     qk_part(st);
     // Operands are read four MFMAs ahead of their products, the first K
-    // operands while the last P.V products run.
+    // operands while the last P.V products run (an operand of V^T is two reads,
+    // one of K is one; each product is D / 8 MFMAs).
     __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
-    for (int i = 0; i < 12; ++i) {
+    for (int i = 0; i < D / 8 - 4; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < D / 8; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
@@ -1027,7 +609,19 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
             pf[i] = fast_exp2(fmaf(sacc[blk][8 * hf + i], c, -m_use));
             pv[i] = f32_to_bf16(pf[i]);
           }
-          psum[2 * blk + hf] = ((pf[0] + pf[1]) + (pf[2] + pf[3])) + ((pf[4] + pf[5]) + (pf[6] + pf[7]));
+          if constexpr (D == 64) {
+            // rounded P, as P.V takes it: two chains of two dot products with 1
+            const bf16x2 ones = {(bf16)1.f, (bf16)1.f};
+            auto pair = [&](auto j, float acc) {
+              constexpr int J = decltype(j)::value;
+              return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, J, J + 1), ones, acc, false);
+            };
+            using std::integral_constant;
+            psum[2 * blk + hf] = pair(integral_constant<int, 2>{}, pair(integral_constant<int, 0>{}, 0.f)) +
+                                 pair(integral_constant<int, 6>{}, pair(integral_constant<int, 4>{}, 0.f));
+          } else {
+            psum[2 * blk + hf] = ((pf[0] + pf[1]) + (pf[2] + pf[3])) + ((pf[4] + pf[5]) + (pf[6] + pf[7]));
+          }
           pop[2 * blk + hf] = pv;
         }
       return (psum[0] + psum[1]) + (psum[2] + psum[3]);
@@ -1069,26 +663,27 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   // V(1) ..; waves 0-3 take the barrier of tile t after V(t), waves 4-7 after
   // MFMA(t), so a SIMD's two waves alternate without a barrier between their
   // phases.  The barrier of tile t follows each wave's wait for its loads of
-  // tile t+1 (those of tile t+2 may stay in flight); after it, tile t+3 goes
-  // into the stage of tile t-1, whose last reads (P.V of tile t-1, in MFMA(t))
-  // every wave has completed by then.
+  // tile t+1 (with loads three tiles ahead those of t+2 may stay in flight);
+  // after it, tile t + kAhead goes into the K slot of tile t (two slots) or an
+  // older one and the V slot of tile t-1: their last reads (K(t) Q^T and P.V of
+  // tile t-1, both in MFMA(t)) every wave has completed by then.
   auto barrier = [&]() {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
   auto sync_tile = [&](int t) {
-    if (t + 2 < n) __builtin_amdgcn_s_waitcnt(kWaitVm4);
+    if (Shape::kAhead > 2 && t + 2 < n) __builtin_amdgcn_s_waitcnt(wait_vm(2 * Shape::kLoads));
     else __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
     barrier();
-    if (t + kPPStages - 1 < n) issue_tile(t + kPPStages - 1);
+    if (t + Shape::kAhead < n) issue_tile(t + Shape::kAhead);
   };
 
-  // Prologue: tiles 0 .. kPPStages-2 and this wave's Q rows in flight, then
+  // Prologue: tiles 0 .. Shape::kAhead-1 and this wave's Q rows in flight, then
   // everything complete (the explicit full wait also tells the compiler that
   // the Q registers are ready, so it adds no wait of its own inside the loop).
-  for (int u = 0; u < kPPStages - 1 && u < n; ++u) issue_tile(u);
+  for (int u = 0; u < Shape::kAhead && u < n; ++u) issue_tile(u);
 #pragma unroll
   for (int s = 0; s < kKSteps; ++s) {
     u32x4 x = {0u, 0u, 0u, 0u};
@@ -1102,29 +697,27 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   if (grp == 1) sync_tile(0);
   valu_phase(0);
   if (grp == 0) sync_tile(0);
-  // Tiles 1, 2, 3, 4, 5, .. use stages 1, 2, 3, 0, 1, ..: the loop runs four
-  // tiles per pass with each stage a compile-time constant (its operand
-  // addresses are then immediate offsets), the last n - 1 mod 4 tiles with
-  // the stage computed.
-  auto tile_step = [&](int t, int st) {
-    mfma_phase(t, st);
+  // Tile t uses slots t % kKSlots and t % kVSlots: the loop runs kUnroll tiles
+  // per pass with each slot a compile-time constant (its operand addresses are
+  // then immediate offsets), the remaining tiles with the slots computed.
+  // phase = t modulo kUnroll
+  auto tile_step = [&](int t, int phase) {
+    mfma_phase(phase % Shape::kKSlots, (phase + Shape::kUnroll - 1) % Shape::kVSlots);
     if (grp == 1) sync_tile(t);
     valu_phase(t);
     if (grp == 0) sync_tile(t);
   };
   int t = 1;
-  for (; t + 3 < n; t += 4) {
-    tile_step(t, 1);
-    tile_step(t + 1, 2);
-    tile_step(t + 2, 3);
-    tile_step(t + 3, 0);
+  for (; t + Shape::kUnroll <= n; t += Shape::kUnroll) {
+#pragma unroll
+    for (int u = 0; u < Shape::kUnroll; ++u) tile_step(t + u, (u + 1) % Shape::kUnroll);
   }
-  for (; t < n; ++t) tile_step(t, t % kPPStages);
-  pv_part((n - 1) % kPPStages);
+  for (; t < n; ++t) tile_step(t, t % Shape::kUnroll);
+  pv_part((n - 1) % Shape::kVSlots);
   // every wave passed the barrier of tile n-1 after its loads of the last
   // tiles completed, so the ring holds them
   if (APPEND && writer)
-    for (int u = max(n - kPPStages, 0); u < n; ++u) append_tile(u, u % kPPStages);
+    for (int u = max(n - ROWS / kBN, 0); u < n; ++u) append_tile(u);
 
   // Epilogue: normalise by the row sum, store.
   const float l_tot = xor32_sum(l_run);
@@ -1158,7 +751,7 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   }
 }
 
-// Dynamic tail of the d_head-128 launches.  The XCDs run at different speeds
+// Dynamic tail of the d_head-128 launches (n_dyn > 0).  The XCDs run at different speeds
 // under this load (several percent apart), and the slowest sets the end of a
 // launch whose items are dealt to them in equal shares.  The first items keep
 // their static XCD-aware order; the light items at the end (the streaming
@@ -1228,39 +821,49 @@ __device__ __forceinline__ int pp_take(int slot, int n, int n_dyn) {
   return __builtin_amdgcn_readfirstlane(s_item);
 }
 
+// The launches that have a dynamic tail: few large workgroups per CU.  (Its
+// four bytes of LDS would also leave one workgroup a CU for 128 rows of
+// d_head 128, whose rings take half of the LDS.)
+template <int D, int ROWS>
+constexpr bool kPPDynamic = D == 128 && ROWS == 256;
+
 // One head type: workgroups [0, n_static) take items [0, n_static) in the
 // XCD-aware order, the n_dyn others the tail items [n_static, n_static + n_tail).
-template <bool STREAM, bool OUT_F32, bool APPEND>
-__global__ __launch_bounds__(512, 1) void prefill_pp_kernel(PrefillArgs a, int n_static, int n_tail, int n_dyn,
-                                                            int slot) {
-  __shared__ __align__(1024) PPRing ring;
+template <int D, int ROWS, bool STREAM, bool OUT_F32, bool APPEND>
+__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_kernel(PrefillArgs a, int n_static, int n_tail,
+                                                                            int n_dyn, int slot) {
+  __shared__ __align__(1024) PPRing<D, ROWS> ring;
   int w = blockIdx.x;
-  if (w >= n_static) {
-    w = pp_take(slot, n_tail, n_dyn);
-    if (w < 0) return;
-    w += n_static;
+  if constexpr (kPPDynamic<D, ROWS>) {
+    if (w >= n_static) {
+      w = pp_take(slot, n_tail, n_dyn);
+      if (w < 0) return;
+      w += n_static;
+    }
   }
-  prefill_pp_body<STREAM, OUT_F32, APPEND>(a, w, ring);
+  prefill_pp_body<D, ROWS, STREAM, OUT_F32, APPEND>(a, w, ring);
 }
 
 // Both head types of a layer in one launch: workgroups [0, n_ret) take the
 // retrieval items, [ret_pad, ret_pad + n_dyn) the n_str streaming ones
 // through the queues (ret_pad = n_ret rounded up to the 8 XCDs, so both item
-// spaces keep their XCD-aware order).  The light streaming items are
-// dispatched last and fill the CUs that the causal retrieval items leave
-// idle at the end.
-template <bool OUT_F32, bool APPEND>
-__global__ __launch_bounds__(512, 1) void prefill_pp_mixed_kernel(PrefillArgs ar, PrefillArgs as, int n_ret,
-                                                                  int ret_pad, int n_str, int n_dyn, int slot) {
-  __shared__ __align__(1024) PPRing ring;
+// spaces keep their XCD-aware order), or with n_dyn = 0 [ret_pad, ret_pad +
+// n_str) take them in order.  The light streaming items are dispatched last
+// and fill the CUs that the causal retrieval items leave idle at the end.
+template <int D, int ROWS, bool OUT_F32, bool APPEND>
+__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_mixed_kernel(PrefillArgs ar, PrefillArgs as,
+                                                                                  int n_ret, int ret_pad, int n_str,
+                                                                                  int n_dyn, int slot) {
+  __shared__ __align__(1024) PPRing<D, ROWS> ring;
   const int wg = blockIdx.x;
   if (wg < n_ret) {
-    prefill_pp_body<false, OUT_F32, APPEND>(ar, wg, ring);
+    prefill_pp_body<D, ROWS, false, OUT_F32, APPEND>(ar, wg, ring);
     return;
   }
   if (wg < ret_pad) return;
-  const int w = pp_take(slot, n_str, n_dyn);
-  if (w >= 0) prefill_pp_body<true, OUT_F32, APPEND>(as, w, ring);
+  int w = wg - ret_pad;
+  if constexpr (kPPDynamic<D, ROWS>) w = pp_take(slot, n_str, n_dyn);
+  if (w >= 0) prefill_pp_body<D, ROWS, true, OUT_F32, APPEND>(as, w, ring);
 }
 
 static std::atomic<uint32_t> g_sched_next{0};
@@ -1268,25 +871,19 @@ static int pp_slot() { return (int)(g_sched_next.fetch_add(1, std::memory_order_
 // Workgroups that take part in a dynamic tail of n items.
 static int pp_n_dyn(int n) { return (int)((1.f + kStreamSlack) * n / 8 + 1) * 8; }
 
-template <int D, bool STREAM, bool OUT_F32>
+template <int D, int ROWS, bool STREAM, bool OUT_F32>
 static hipError_t launch_bf16(const PrefillArgs& a, hipStream_t s) {
   const int grid = a.n_qblocks * a.n_kv * a.gs * a.B;
-  if constexpr (D == kPPD) {
-    // the first half of the items (a multiple of 8) static, the rest dynamic
-    const int n_static = grid / 16 * 8, n_tail = grid - n_static, n_dyn = pp_n_dyn(n_tail);
-    const int slot = pp_slot();
-    if (a.append)
-      hipLaunchKernelGGL((prefill_pp_kernel<STREAM, OUT_F32, true>), dim3(n_static + n_dyn), dim3(512), 0, s, a,
-                         n_static, n_tail, n_dyn, slot);
-    else
-      hipLaunchKernelGGL((prefill_pp_kernel<STREAM, OUT_F32, false>), dim3(n_static + n_dyn), dim3(512), 0, s, a,
-                         n_static, n_tail, n_dyn, slot);
-  } else {
-    if (a.append)
-      hipLaunchKernelGGL((prefill_bf16_kernel<D, STREAM, OUT_F32, true>), dim3(grid), dim3(kWaves * kWave), 0, s, a);
-    else
-      hipLaunchKernelGGL((prefill_bf16_kernel<D, STREAM, OUT_F32, false>), dim3(grid), dim3(kWaves * kWave), 0, s, a);
-  }
+  // with a dynamic tail the first half of the items (a multiple of 8) is static
+  constexpr bool kDyn = kPPDynamic<D, ROWS>;
+  const int n_static = kDyn ? grid / 16 * 8 : grid, n_tail = grid - n_static;
+  const int n_dyn = kDyn ? pp_n_dyn(n_tail) : 0;
+  const int slot = kDyn ? pp_slot() : 0;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(n_static + n_dyn), dim3(2 * ROWS), 0, s, a, n_static, n_tail, n_dyn, slot);
+  };
+  if (a.append) go(prefill_pp_kernel<D, ROWS, STREAM, OUT_F32, true>);
+  else go(prefill_pp_kernel<D, ROWS, STREAM, OUT_F32, false>);
   return hipGetLastError();
 }
 
@@ -1298,51 +895,78 @@ static hipError_t launch_f32(const PrefillArgs& a, hipStream_t s) {
 }
 
 // The mixed launch pays where the retrieval items fill only a few rounds of
-// the 256 CUs (one 512-thread workgroup per CU): their causal tail is then a
+// the 256 CUs (one workgroup of 256 rows per CU): their causal tail is then a
 // sizeable part of the launch.  Its retrieval path is compiled together with
 // the streaming one and runs ~1-2% slower per tile, so long launches keep two
 // kernels: measured on the 28/4-head d_head-128 layer, 1.6% faster at 32768
 // tokens (7 rounds), even at 65536, 0.5-1.7% slower from 131072 on.
 constexpr int kMixedMaxRetItems = 8 * 256;
 
-bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d) {
+bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d, int rows) {
   const int64_t n_ret = (int64_t)ar.n_qblocks * ar.n_kv * ar.gs * ar.B;
-  return dtype == 0 && d == kPPD && n_ret <= kMixedMaxRetItems;
+  return dtype == 0 && (d == 64 || n_ret * rows <= (int64_t)kMixedMaxRetItems * 256);
 }
 
-hipError_t launch_prefill_mixed(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, hipStream_t s) {
+template <int D, int ROWS>
+static hipError_t launch_mixed_d(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, hipStream_t s) {
   const int n_ret = ar.n_qblocks * ar.n_kv * ar.gs * ar.B;
   const int n_str = as.n_qblocks * as.n_kv * as.gs * as.B;
   const int ret_pad = (n_ret + 7) / 8 * 8;
-  const int n_dyn = pp_n_dyn(n_str);
-  const int slot = pp_slot();
-  const dim3 grid(ret_pad + n_dyn), blk(512);
+  constexpr bool kDyn = kPPDynamic<D, ROWS>;
+  const int n_dyn = kDyn ? pp_n_dyn(n_str) : 0;
+  const int slot = kDyn ? pp_slot() : 0;
+  const dim3 grid(ret_pad + (kDyn ? n_dyn : n_str)), blk(2 * ROWS);
   const bool app = ar.append;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, blk, 0, s, ar, as, n_ret, ret_pad, n_str, n_dyn, slot);
   };
   if (out_f32) {
-    if (app) go(prefill_pp_mixed_kernel<true, true>);
-    else go(prefill_pp_mixed_kernel<true, false>);
+    if (app) go(prefill_pp_mixed_kernel<D, ROWS, true, true>);
+    else go(prefill_pp_mixed_kernel<D, ROWS, true, false>);
   } else {
-    if (app) go(prefill_pp_mixed_kernel<false, true>);
-    else go(prefill_pp_mixed_kernel<false, false>);
+    if (app) go(prefill_pp_mixed_kernel<D, ROWS, false, true>);
+    else go(prefill_pp_mixed_kernel<D, ROWS, false, false>);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, bool streaming,
+// Query rows per workgroup.  d_head 64: 128 rows, three workgroups a CU (its
+// products are half as long next to the same softmax, so a third wave per SIMD
+// pays: 32 query / 8 KV heads, half of them streaming, 4 x 4000 tokens 220 us;
+// 250 with 256 rows, 259 with 384 rows of 12 waves).  d_head 128: 256 rows where
+// prompts are long (a K/V tile is fetched for twice the rows: 32768 tokens 3.87
+// ms, 4.15 with 128), 128 where items are few or uneven: one prompt of 701 tokens
+// 28.6 against 36.6 us, 4 x 4000 388 against 398, 8192 tokens even, 16 packed
+// prompts of 512-24576 tokens 13.2 against 13.7 ms, 12 of 500-9000 1.81 against
+// 1.99; 4 packed of 8000-24000 4.38 against 4.33.
+int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed) {
+  if (dtype == 1) return kPrefillRowsF32;
+  if (d == 64) return 128;
+  if (!packed) return longest <= 8192 ? 128 : 256;
+  return n_rows <= batch * (batch >= 8 ? 16384 : 8192) ? 128 : 256;
+}
+
+hipError_t launch_prefill_mixed(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, int d, int rows,
+                                hipStream_t s) {
+  if (d == 64) return launch_mixed_d<64, 128>(ar, as, out_f32, s);
+  return rows == 128 ? launch_mixed_d<128, 128>(ar, as, out_f32, s) : launch_mixed_d<128, 256>(ar, as, out_f32, s);
+}
+
+template <int D, int ROWS>
+static hipError_t launch_one_type(const PrefillArgs& a, int out_f32, bool streaming, hipStream_t s) {
+  if (out_f32) return streaming ? launch_bf16<D, ROWS, true, true>(a, s) : launch_bf16<D, ROWS, false, true>(a, s);
+  return streaming ? launch_bf16<D, ROWS, true, false>(a, s) : launch_bf16<D, ROWS, false, false>(a, s);
+}
+
+hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, int rows, bool streaming,
                           hipStream_t s) {
   if (dtype == 1) {  // fp32
     if (d == 64) return streaming ? launch_f32<64, true>(a, s) : launch_f32<64, false>(a, s);
     return streaming ? launch_f32<128, true>(a, s) : launch_f32<128, false>(a, s);
   }
-  if (d == 64) {
-    if (out_f32) return streaming ? launch_bf16<64, true, true>(a, s) : launch_bf16<64, false, true>(a, s);
-    return streaming ? launch_bf16<64, true, false>(a, s) : launch_bf16<64, false, false>(a, s);
-  }
-  if (out_f32) return streaming ? launch_bf16<128, true, true>(a, s) : launch_bf16<128, false, true>(a, s);
-  return streaming ? launch_bf16<128, true, false>(a, s) : launch_bf16<128, false, false>(a, s);
+  if (d == 64) return launch_one_type<64, 128>(a, out_f32, streaming, s);
+  return rows == 128 ? launch_one_type<128, 128>(a, out_f32, streaming, s)
+                     : launch_one_type<128, 256>(a, out_f32, streaming, s);
 }
 
 }  // namespace aoh

@@ -1,0 +1,98 @@
+"""bf16 prefill around the edges of its query blocks, against a plain fp32 reference of the same attention.
+
+Workgroups of 128 query rows (d_head 64; d_head 128 up to 8192 tokens, and packed prompts that are short on average) and
+of 256 (longer prompts of d_head 128), tiles of 64 keys: lengths at and next to multiples of them, a single row, one
+tile, dense and packed, both kinds of mask, the caches against a separate append."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2608_06849_amd import PagedCache, RingCache, aoh_kv_append, aoh_prefill_append, aoh_prefill_varlen
+from tests.helpers import BF16_MAX_ABS, BF16_MEAN_ABS, bits, to_dtype
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+HQ, MASK, N_SINK, WINDOW = 4, [0, 1], 20, 150
+
+
+def reference(q, k, v, chunk):
+    """[T, H, D] bf16 -> [T, Hq, D] fp32."""
+    t = q.shape[0]
+    i = torch.arange(t, device=q.device).view(-1, 1)
+    j = torch.arange(t, device=q.device).view(1, -1)
+    lo = (i // chunk) * chunk - WINDOW if chunk else i - WINDOW + 1
+    masks = [j <= i, (j <= i) & ((j < N_SINK) | (j >= lo))]
+    out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+    for h in range(HQ):
+        g = h // (HQ // len(MASK))
+        s = q[:, h].float() @ k[:, g].float().t().contiguous() / q.shape[-1] ** 0.5
+        out[:, h] = torch.softmax(s.masked_fill(~masks[MASK[g]], -torch.inf), -1) @ v[:, g].float()
+    return out
+
+
+def inputs(t, d, seed):
+    return [to_dtype(synth.gaussian((t, h, d), seed, n), torch.bfloat16).to(DEV)
+            for h, n in ((HQ, "q"), (2, "k"), (2, "v"))]
+
+
+def caches(batch, t, d, seed):
+    pages = (t + 15) // 16
+    table = torch.from_numpy(synth.page_permutation(batch * pages, seed).reshape(batch, pages).copy())
+    full = PagedCache.allocate(batch * pages, 1, d, torch.bfloat16, table)
+    ring = RingCache.allocate(batch, 1, N_SINK, WINDOW, d, torch.bfloat16)
+    for c in (full, ring):
+        c.k.zero_()
+        c.v.zero_()
+    return full, ring
+
+
+def check(got, want, what):
+    err = (got.float() - want).abs()
+    assert err.max() <= BF16_MAX_ABS and err.mean() <= BF16_MEAN_ABS, f"{what}: {err.max()} {err.mean()}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("t", [1, 63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257, 320, 385, 640, 1025])
+def test_block_edges(t, d):
+    q, k, v = inputs(t, d, t + d)
+    for chunk in (0, 100):
+        full, ring = caches(1, t, d, t)
+        out = aoh_prefill_append(q[None], k[None], v[None], MASK, N_SINK, WINDOW, full, ring, chunk=chunk)
+        check(out[0], reference(q, k, v, chunk), f"T {t} d {d} chunk {chunk}")
+        full2, ring2 = caches(1, t, d, t)
+        aoh_kv_append(k[None], v[None], MASK, torch.zeros(1, dtype=torch.int32, device=DEV), full2, ring2, N_SINK,
+                      WINDOW)
+        for a, b in ((full.k, full2.k), (full.v, full2.v), (ring.k, ring2.k), (ring.v, ring2.v)):
+            assert np.array_equal(bits(a), bits(b)), f"T {t} d {d} chunk {chunk}: caches"
+
+
+@pytest.mark.parametrize("t", [8192, 8193, 8449])
+def test_long_prompt(t):
+    # both sides of the change from 128 to 256 query rows
+    q, k, v = inputs(t, 128, t)
+    full, ring = caches(1, t, 128, t)
+    out = aoh_prefill_append(q[None], k[None], v[None], MASK, N_SINK, WINDOW, full, ring)
+    check(out[0], reference(q, k, v, 0), f"T {t}")
+
+
+@pytest.mark.parametrize("d,lens", [
+    (64, [1, 127, 128, 129, 300, 64]), (128, [1, 127, 128, 129, 300, 64]),
+    (128, [9000, 130, 8000]),                             # 256 rows: few prompts, long on average
+    (128, [9000, 1, 257, 64, 65, 128, 700, 31]),          # 128 rows
+])
+def test_packed(d, lens):
+    total = sum(lens)
+    q, k, v = inputs(total, d, total)
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=DEV)
+    full, ring = caches(len(lens), max(lens), d, total)
+    out = aoh_prefill_varlen(q, k, v, cu, max(lens), MASK, N_SINK, WINDOW, kv_full=full, kv_ring=ring)
+    full2, ring2 = caches(len(lens), max(lens), d, total)
+    for i, n in enumerate(lens):
+        s = slice(int(cu[i]), int(cu[i]) + n)
+        check(out[s], reference(q[s], k[s], v[s], 0), f"{lens} sequence {i}")
+        aoh_kv_append(k[None, s], v[None, s], MASK, torch.zeros(1, dtype=torch.int32, device=DEV),
+                      full2.rows(i, i + 1), RingCache(ring2.k[i:i + 1], ring2.v[i:i + 1], ring2.capacity), N_SINK,
+                      WINDOW)
+    for a, b in ((full.k, full2.k), (full.v, full2.v), (ring.k, ring2.k), (ring.v, ring2.v)):
+        assert np.array_equal(bits(a), bits(b)), f"{lens}: caches"
