@@ -473,8 +473,8 @@ size_t aoh_decode_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t d_he
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Anchor extras: score codes [B][Hq][16 * max_pages] (16-bit) and their
-// references [B][Hq][max_pages], final (m, l) [B][Hq][2], and the top-k keys
+// Anchor extras: 16 * max_pages score codes (16-bit) and max_pages references per
+// query head, final (m, l) [B][Hq][2], and the top-k keys
 // and partial histograms per (sequence, KV head) list (sized with Hq lists per
 // sequence, a bound on the retrieval KV heads).
 static size_t anchor_codes_bytes(int64_t B, int64_t Hq, int64_t max_pages) {
@@ -490,13 +490,11 @@ static size_t anchor_ml_bytes(int64_t B, int64_t Hq) { return align256((size_t)(
 static size_t anchor_part_bytes(int64_t B, int64_t Hq) {
   return align256((size_t)(B * Hq * kTopkPasses * kTopkParts * 2048) * sizeof(uint32_t));
 }
-// dummy targets of the score stores: 64 x 8 codes, then 64 references
-static constexpr size_t kCodeDummyBytes = 64 * 8 * sizeof(uint16_t);
-static constexpr size_t kScoreDummyBytes = kCodeDummyBytes + 64 * sizeof(float);
+static constexpr size_t kAnchorSpareBytes = 1280;  // unused; the size of the workspace is part of the interface
 static size_t anchor_extra(int64_t B, int64_t Hq, int64_t max_pages) {
   return anchor_codes_bytes(B, Hq, max_pages) + anchor_refs_bytes(B, Hq, max_pages) +
          anchor_keys_bytes(B, Hq, max_pages) + anchor_ml_bytes(B, Hq) + anchor_part_bytes(B, Hq) +
-         kScoreDummyBytes;
+         kAnchorSpareBytes;
 }
 
 // H2Share roles of a decode call (Sec. "AoH-Guided Sparse Attention"): plain,
@@ -719,9 +717,6 @@ static aoh_status decode_impl(const aoh_tensor* q, const aoh_paged_cache* kv_ful
     ml = reinterpret_cast<float*>(w);
     w += anchor_ml_bytes(B, Hq);
     part = reinterpret_cast<uint32_t*>(w);
-    w += anchor_part_bytes(B, Hq);
-    a.code_dummy = reinterpret_cast<uint16_t*>(w);
-    a.ref_dummy = reinterpret_cast<float*>(w + kCodeDummyBytes);
     a.score_codes = codes;
     a.score_refs = refs;
     a.score_len = max_pages * kPageTokens;

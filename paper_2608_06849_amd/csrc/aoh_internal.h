@@ -105,14 +105,12 @@ struct DecodeArgs {
   // Anchor layer (H2Share): the scaled scores (log2 units) of the paged-cache
   // heads for positions < lens, rounded to multiples of 1 / kScoreCodeScale,
   // each as a 16-bit distance below a reference: score = ref - code /
-  // kScoreCodeScale, with codes [B][Hq][score_len] and one reference per
-  // 16-token block, refs [B][Hq][score_len / 16] (the rounded maximum of the
-  // 32-token chunk the block was scored in).  Distances of 65535 steps and
-  // more saturate at 65535.
+  // kScoreCodeScale, with codes [B][n_kv][score_len / 16][gs][16] and one
+  // reference per 16-token block and head, refs [B][n_kv][score_len / 16][gs]
+  // (the rounded maximum of the 32-token chunk the block was scored in).
+  // Distances of 65535 steps and more saturate at 65535.
   uint16_t* score_codes;
   float* score_refs;
-  uint16_t* code_dummy;         // 64 x 8 codes written by lanes without a query head
-  float* ref_dummy;             // 64 references written by those lanes
   int32_t score_len;
   // Reuse layer (H2Share): paged-cache items attend to borrowed positions
   // sel[b][sel_rank[j]][0..n_sel) (ascending, -1 = none) of KV head j of the
@@ -214,8 +212,8 @@ hipError_t launch_classify(const ClassifyArgs& a, int d, hipStream_t s);
 // KV head j of the list), the n_sel positions of highest group-mean attention
 // probability, ascending, padded with -1.
 struct TopkArgs {
-  const uint16_t* score_codes;  // [B][Hq][score_len] (DecodeArgs::score_codes)
-  const float* score_refs;      // [B][Hq][score_len / 16]
+  const uint16_t* score_codes;  // DecodeArgs::score_codes, score_refs
+  const float* score_refs;
   uint32_t* keys;               // [B][n_kv][score_len] ranking keys of the lists
   const float* ml;              // [B][Hq][2] final (m, l)
   const int32_t* lens;

@@ -25,15 +25,38 @@
 
 namespace aoh {
 
+// A wave's score codes of the anchor layer on their way to memory: its last
+// chunks in LDS, in the order of the global arrays ([block][head][16] codes,
+// [block][head] references), written out when the buffer is full and at the end
+// of the wave's range as whole lines.  Stored per chunk (256 bytes of codes and
+// 32 of references for four heads), the stores held up the read stream: the
+// split pass of 8 x 131072 tokens took 435-445 us against 338 without scores, and
+// 382 this way (396 with stores that are not non-temporal).
+struct CodeBuf {
+  uint16_t* codes;  // LDS
+  float* refs;      // LDS, after the codes
+  int blocks;       // capacity (even)
+};
+
+template <int D>
+__device__ __forceinline__ CodeBuf code_buf(void* lds, int gs) {
+  constexpr int kBytes = (D / 16) * kWave * 16;  // one wave's partials take as much
+  CodeBuf b;
+  b.blocks = kBytes / (gs * (kPage * 2 + 4)) & ~1;
+  b.codes = static_cast<uint16_t*>(lds);
+  b.refs = reinterpret_cast<float*>(b.codes + b.blocks * gs * kPage);
+  return b;
+}
+
 // Folds one 32-token chunk (token blocks c and c + 1 of the cache row; tokens
-// at or past tok_end masked, none of them at or past blk_end * 16 kept as a
-// score) into a wave's running softmax state: K rows in kcur, the V^T operand
-// in vcur (zeroed where masked), Q^T in qreg.
+// at or past tok_end masked) into a wave's running softmax state: K rows in
+// kcur, the V^T operand in vcur (zeroed where masked), Q^T in qreg.  SCORES:
+// the scores go to blocks `slot` and slot + 1 of the buffer.
 template <int D, bool SCORES>
 __device__ __forceinline__ void fold_chunk(const DecodeArgs& a, const u32x4 (&kcur)[2][D / 32],
                                            u32x4 (&vcur)[D / 16], const bf16x8 (&qreg)[D / 32], int c, int tok_end,
-                                           int blk_end, bool head_ok, uint16_t* code_row, float* ref_row,
-                                           f32x4 (&acc)[D / 16], float& m_run, float& l_run) {
+                                           bool head_ok, const CodeBuf& buf, int slot, f32x4 (&acc)[D / 16],
+                                           float& m_run, float& l_run) {
   constexpr int kKSteps = D / 32;
   constexpr int kDimBlocks = D / 16;
   const int lane = threadIdx.x & (kWave - 1);
@@ -70,13 +93,7 @@ __device__ __forceinline__ void fold_chunk(const DecodeArgs& a, const u32x4 (&kc
     // blocks; a kept score therefore reads back as its own grid point
     // whatever chunk it was scored in (equal scores stay equal), unless its
     // distance saturates.  Masked positions (beyond the valid length, never
-    // read by the selection) saturate.  Every lane issues the same stores in
-    // every chunk (a fixed count, so the compiler's wait for the prefetched
-    // chunk stays exact): lanes without a query head, and lanes whose tokens
-    // lie past the range's last block (the missing second block of a range
-    // with an odd block count, which at the end of a full row would be the
-    // next row's first positions), write to a dummy area.
-    const bool keep = head_ok && tok0 < blk_end * kPage;
+    // read by the selection) saturate.
     // grid points are integer-valued floats; mx is one of the scores, so
     // every distance is >= 0; -inf scores give +inf, clamped before the
     // conversion
@@ -88,10 +105,12 @@ __device__ __forceinline__ void fold_chunk(const DecodeArgs& a, const u32x4 (&kc
       const uint32_t hi = (uint32_t)fminf(top - rintf(x[2 * j + 1] * kScoreCodeScale), 65535.f);
       w[j] = lo | (hi << 16);
     }
-    uint16_t* cp = keep ? code_row + tok0 : a.code_dummy + 8 * lane;
-    *reinterpret_cast<u32x4*>(cp) = u32x4{w[0], w[1], w[2], w[3]};
-    // lane groups 0 and 2 start the chunk's two blocks
-    if ((G & 1) == 0) *(keep ? ref_row + tok0 / kPage : a.ref_dummy + lane) = top * (1.f / kScoreCodeScale);
+    if (head_ok) {
+      const int at = (slot + (G >> 1)) * a.gs + (lane & 15);  // (block, head)
+      *reinterpret_cast<u32x4*>(buf.codes + at * kPage + 8 * (G & 1)) = u32x4{w[0], w[1], w[2], w[3]};
+      // lane groups 0 and 2 start the chunk's two blocks
+      if ((G & 1) == 0) buf.refs[at] = top * (1.f / kScoreCodeScale);
+    }
   }
   const float m_new = fmaxf(m_run, mx);  // finite: every chunk holds a valid token
   const float alpha = fast_exp2(m_run - m_new);
@@ -132,7 +151,7 @@ __device__ __forceinline__ void fold_chunk(const DecodeArgs& a, const u32x4 (&kc
 template <int D, bool RING, bool SCORES = false, bool APPEND = false>
 __device__ __forceinline__ void decode_split_body(const DecodeArgs& a, const CacheView& cv, int b, int kvl,
                                                   int len, int blk0, int blk_lim, f32x4 (&acc)[D / 16],
-                                                  float& m_out, float& l_out) {
+                                                  float& m_out, float& l_out, void* lds = nullptr) {
   constexpr int kKSteps = D / 32;   // 32-dim k-steps for Q K^T
   constexpr int kDimBlocks = D / 16;
   const int g = cv.kv_heads[kvl];
@@ -248,6 +267,10 @@ __device__ __forceinline__ void decode_split_body(const DecodeArgs& a, const Cac
     }
   }
 
+  CodeBuf buf = {};
+  if (SCORES) buf = code_buf<D>(lds, a.gs);
+  int buf0 = blk0;  // first buffered block
+
   int ent[2];
   fetch_entries(blk0, ent);
   load_chunk(ent);
@@ -266,10 +289,17 @@ __device__ __forceinline__ void decode_split_body(const DecodeArgs& a, const Cac
       if (c + 4 < blk_end) fetch_entries(c + 4, ent);  // entries of chunk c + 4
     }
 
-    fold_chunk<D, SCORES>(a, kcur, vcur, qreg, c, tok_end, blk_end, head_ok,
-                          SCORES ? a.score_codes + ((int64_t)b * a.Hq + hq) * a.score_len : nullptr,
-                          SCORES ? a.score_refs + ((int64_t)b * a.Hq + hq) * (a.score_len / kPage) : nullptr, acc,
-                          m_run, l_run);
+    fold_chunk<D, SCORES>(a, kcur, vcur, qreg, c, tok_end, head_ok, buf, c - buf0, acc, m_run, l_run);
+    if (SCORES && (c + 2 - buf0 == buf.blocks || c + 2 >= blk_end)) {
+      // this wave's buffered blocks [buf0, end) to memory
+      const int n = (min(c + 2, blk_end) - buf0) * a.gs;
+      const int64_t row = ((int64_t)b * cv.n_kv + kvl) * a.gs * (a.score_len / kPage) + (int64_t)buf0 * a.gs;
+      for (int i = lane; i < 2 * n; i += kWave)
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(buf.codes + 8 * i),
+                                    reinterpret_cast<u32x4*>(a.score_codes + row * kPage + 8 * i));
+      for (int i = lane; i < n; i += kWave) a.score_refs[row + i] = buf.refs[i];
+      buf0 = c + 2;
+    }
   }
 
   // Partial results of this split: m (log2 units), l, acc[D] for each head.
@@ -490,6 +520,7 @@ template <int D, int MODE>
 __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_split_bf16_kernel(DecodeArgs a) {
   constexpr int kDimBlocks = D / 16;
   __shared__ f32x4 s_acc[kSplitWaves][kDimBlocks][kWave];
+  __shared__ f32x4 s_code[MODE == 1 ? kSplitWaves : 1][MODE == 1 ? kDimBlocks * kWave : 1];  // CodeBuf of each wave
   __shared__ float s_m[kSplitWaves][kWave];
   __shared__ float s_l[kSplitWaves][kWave];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -517,7 +548,7 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_split_bf16_kern
       decode_sparse_body<D>(a, a.full, b, kvl, split, acc, m, l);
     else
       decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, b, kvl, len, blk0, blk0 + cv.split_blocks, acc,
-                                                        m, l);
+                                                        m, l, s_code[MODE == 1 ? wave : 0]);
   }
   const int col = lane & 15;
   const int hq = cv.kv_heads[kvl] * a.gs + col;
@@ -632,6 +663,7 @@ template <int D, int MODE>
 __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_ws_kernel(DecodeArgs a) {
   constexpr int kDimBlocks = D / 16;
   __shared__ f32x4 s_acc[kSplitWaves][kDimBlocks][kWave];
+  __shared__ f32x4 s_code[MODE == 1 ? kSplitWaves : 1][MODE == 1 ? kDimBlocks * kWave : 1];  // CodeBuf of each wave
   __shared__ float s_m[kSplitWaves][kWave];
   __shared__ float s_l[kSplitWaves][kWave];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -662,7 +694,9 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_ws_kernel(Decod
     float m = -INFINITY, l = 0.f;
     if (c0 < c1) {
       if (it.ring) decode_split_body<D, true, false, MODE == 3>(a, a.ring, it.b, it.kvl, len, c0, c1, acc, m, l);
-      else decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, it.b, it.kvl, len, c0, c1, acc, m, l);
+      else
+        decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, it.b, it.kvl, len, c0, c1, acc, m, l,
+                                                          s_code[MODE == 1 ? wave : 0]);
     }
     const int col = lane & 15;
     merge_waves_store<D>(a, acc, m, l, s_acc, s_m, s_l, col < a.gs, (int64_t)(w + it.idx) * a.gs + col);
@@ -879,7 +913,9 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_many_kernel(Dec
     for (int nb = 0; nb < kDimBlocks; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
     if (it.ring) decode_split_body<D, true, false, MODE == 3>(a, a.ring, it.b, it.kvl, len, s0, s1, acc, m, l);
-    else decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, it.b, it.kvl, len, s0, s1, acc, m, l);
+    else  // the score codes pass through the wave's second piece, which only its last segment fills
+      decode_split_body<D, false, MODE == 1, MODE == 3>(a, a.full, it.b, it.kvl, len, s0, s1, acc, m, l,
+                                                        s_acc[2 * wave + 1]);
     if (s0 == 0 && s1 == it.len) {  // the whole item
       const int hq = (it.ring ? a.ring : a.full).kv_heads[it.kvl] * a.gs + col;
       if (col < a.gs) {

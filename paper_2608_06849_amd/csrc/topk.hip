@@ -166,10 +166,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
   }
   __syncthreads();
   uint32_t* my_hist = hist[t & (kHistCopies - 1)];
-  const int64_t row = a.score_len;
-  const int64_t head0 = (int64_t)b * a.Hq + (int64_t)g * a.gs;
-  const uint16_t* c0 = a.score_codes + head0 * row;
-  const float* r0 = a.score_refs + head0 * (row / 16);
+  const int64_t group = ((int64_t)b * a.n_kv + blockIdx.y) * a.gs * a.score_len;
+  const uint16_t* c0 = a.score_codes + group;  // [block][head][16]
+  const float* r0 = a.score_refs + group / 16;  // [block][head]
   for (int j = v.seg0 + t; j < v.seg1; j += kTopkThreads) {
     uint32_t key;
     if (PASS == 0) {
@@ -177,7 +176,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
       // computed exactly, so equal kept scores give equal keys
       float p = 0.f;
       for (int h = 0; h < a.gs; ++h) {
-        const float xq = r0[h * (row / 16) + j / 16] - (float)c0[h * row + j] * (1.f / kScoreCodeScale);
+        const int64_t at = (int64_t)(j / 16) * a.gs + h;
+        const float xq = r0[at] - (float)c0[at * 16 + j % 16] * (1.f / kScoreCodeScale);
         p += fast_exp2(xq - s_m[h]) * s_il[h];
       }
       key = __builtin_bit_cast(uint32_t, p) & kKeyMask;
