@@ -573,7 +573,20 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_split_bf16_kern
 // covered by workgroups first_i..last_i, has its partials in slots
 // first_i + i .. last_i + i (items are contiguous, so no two items share a
 // slot): at most workgroups + items slots of gs heads each.
-constexpr int kWsMinBlocks = 16;  // smallest range a workgroup takes
+// Smallest range a workgroup takes: kWsShortBlocks while that leaves at most one
+// workgroup per CU, kWsMinBlocks beyond.  A short step is a chain of memory
+// latencies, which a wave with one 32-token chunk ends soonest; a long one pays
+// for more partials.  28 layers of one sequence of 4093 tokens: 286-290 us with
+// ranges of 4 blocks, 330 with 8, 374 with 16, 352 with 2 or 3; 16 layers of 4
+// sequences of 2000-4000: 273 with at most one workgroup per CU, 281 with two.
+constexpr int kWsShortBlocks = 4;
+constexpr int kWsMinBlocks = 16;
+
+__device__ __forceinline__ int ws_n_wg(int total, int n_cu, int max_wg) {
+  const int many = (total + kWsShortBlocks - 1) / kWsShortBlocks;
+  const int few = (total + kWsMinBlocks - 1) / kWsMinBlocks;
+  return min(max_wg, max(1, max(few, min(many, n_cu))));
+}
 
 struct WsPlan {
   int nb_tot, nbr_tot;  // paged / ring blocks summed over the sequences
@@ -614,7 +627,7 @@ __device__ __forceinline__ WsPlan ws_plan(const int32_t* lens, int B, int max_pa
   p.nb_tot = __builtin_amdgcn_readlane(ip, kWave - 1);
   p.nbr_tot = __builtin_amdgcn_readlane(iq, kWave - 1);
   p.total = n_ret * p.nb_tot + n_str * p.nbr_tot;
-  const int n_wg = min(2 * n_cu, max(1, (p.total + kWsMinBlocks - 1) / kWsMinBlocks));
+  const int n_wg = ws_n_wg(p.total, n_cu, 2 * n_cu);
   p.n_old = min(n_wg, n_cu);
   p.n_young = n_wg - p.n_old;
   const int64_t weight = 4 * (int64_t)p.n_old + 3 * (int64_t)p.n_young;
@@ -724,7 +737,7 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_ws_kernel(Decod
 //
 // The ranges of the two rounds are those of decode_ws_kernel.  For few items
 // that kernel's plan, which every wave holds in registers, starts faster (9.5 us
-// a launch against 12 for one sequence of 4093 tokens).  For many, its barriers
+// a launch against 12 for one sequence of 4093 tokens in ranges of 16 blocks).  For many, its barriers
 // and workspace partials at every item cost more, as do fixed splits of the
 // capacity, of which most are empty when lengths differ: 96 sequences of
 // 200-8000 tokens, 8 KV heads of width 128, capacity 8192: 160 us a step here,
@@ -802,7 +815,7 @@ __device__ __forceinline__ ManyPlan many_plan(const DecodeArgs& a, ManyTables& t
   ManyPlan p;
   p.paged_end = a.full.n_kv * __builtin_amdgcn_readfirstlane(tb.pre[0][a.B]);
   p.total = p.paged_end + a.ring.n_kv * __builtin_amdgcn_readfirstlane(tb.pre[1][a.B]);
-  const int n_wg = min(a.many_wgs, max(1, (p.total + kWsMinBlocks - 1) / kWsMinBlocks));
+  const int n_wg = ws_n_wg(p.total, a.ws_cu, a.many_wgs);
   p.n_old = min(n_wg, a.ws_cu);
   p.n_young = n_wg - p.n_old;
   const uint32_t weight = 4 * p.n_old + 3 * p.n_young;  // total < 2^29
