@@ -169,23 +169,54 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
   const int64_t group = ((int64_t)b * a.n_kv + blockIdx.y) * a.gs * a.score_len;
   const uint16_t* c0 = a.score_codes + group;  // [block][head][16]
   const float* r0 = a.score_refs + group / 16;  // [block][head]
-  for (int j = v.seg0 + t; j < v.seg1; j += kTopkThreads) {
-    uint32_t key;
+  // Eight consecutive positions (half a block: 16 bytes of codes a head) or four
+  // (16 bytes of keys) a thread (32 lists of 131000 positions: 15.6 and 8.0 us the
+  // two passes, 18.9 and 11.0 with one position a thread); segments start at multiples of 4096.  Codes past
+  // the segment's end lie in the padded row and are not used.
+  constexpr int kRun = PASS == 0 ? 8 : 4;
+  for (int j0 = v.seg0 + kRun * t; j0 < v.seg1; j0 += kRun * kTopkThreads) {
+    uint32_t key[kRun];
     if (PASS == 0) {
       // score = ref - code / kScoreCodeScale (log2 units): a grid point,
       // computed exactly, so equal kept scores give equal keys
-      float p = 0.f;
+      float p[kRun];
+#pragma unroll
+      for (int i = 0; i < kRun; ++i) p[i] = 0.f;
       for (int h = 0; h < a.gs; ++h) {
-        const int64_t at = (int64_t)(j / 16) * a.gs + h;
-        const float xq = r0[at] - (float)c0[at * 16 + j % 16] * (1.f / kScoreCodeScale);
-        p += fast_exp2(xq - s_m[h]) * s_il[h];
+        const int64_t at = (int64_t)(j0 / 16) * a.gs + h;
+        const float ref = r0[at], m = s_m[h], il = s_il[h];
+        const u32x4 c = ld16(c0 + at * 16 + j0 % 16);
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) {
+          const uint32_t code = (c[i / 2] >> (16 * (i % 2))) & 0xffffu;
+          const float xq = ref - (float)code * (1.f / kScoreCodeScale);
+          p[i] += fast_exp2(xq - m) * il;
+        }
       }
-      key = __builtin_bit_cast(uint32_t, p) & kKeyMask;
-      v.keys[j] = key;
+#pragma unroll
+      for (int i = 0; i < kRun; ++i) key[i] = __builtin_bit_cast(uint32_t, p[i]) & kKeyMask;
+      if (j0 + kRun <= v.seg1) {
+#pragma unroll
+        for (int i = 0; i < kRun; i += 4) st16(v.keys + j0 + i, u32x4{key[i], key[i + 1], key[i + 2], key[i + 3]});
+      } else {
+#pragma unroll
+        for (int i = 0; i < kRun; ++i)
+          if (j0 + i < v.seg1) v.keys[j0 + i] = key[i];
+      }
     } else {
-      key = v.keys[j];
+      if (j0 + kRun <= v.seg1) {
+        const u32x4 w = ld16(v.keys + j0);
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) key[i] = w[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < kRun; ++i) key[i] = j0 + i < v.seg1 ? v.keys[j0 + i] : 0u;
+      }
     }
-    if ((key & pmask) == prefix) atomicAdd(&my_hist[(key >> kShift[PASS]) & (kBins[PASS] - 1)], 1u);
+#pragma unroll
+    for (int i = 0; i < kRun; ++i)
+      if (j0 + i < v.seg1 && (key[i] & pmask) == prefix)
+        atomicAdd(&my_hist[(key[i] >> kShift[PASS]) & (kBins[PASS] - 1)], 1u);
   }
   __syncthreads();
   uint32_t* dst = v.my_part + (int64_t)PASS * kTopkParts * 2048;
