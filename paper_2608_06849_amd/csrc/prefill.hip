@@ -168,8 +168,9 @@ __global__ __launch_bounds__(kPrefillRowsF32) void prefill_f32_kernel(PrefillArg
 //    apart: the barrier comes after the vector phase for waves 0-3, after the
 //    MFMA phase for waves 4-7.  With 128 rows the waves of different
 //    workgroups on a SIMD interleave their phases.
-//    The loop has a single path (a tile with no visible key for a wave
-//    yields P = 0), so the accumulators never move between registers.
+//    The loop has a single path, so the accumulators never move between
+//    registers: a tile with no visible key for a wave yields P = 0 (d_head 128),
+//    or lies outside the loop's range of tiles (64).
 //  * The fused cache append writes the block's own (diagonal) tiles after
 //    the loop, from the ring, which still holds them.
 //  * Workgroups are ordered so that the query heads of one KV group and query
@@ -542,9 +543,10 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
       pp_write_tile<D, STREAM>(a, ring.k[t % Shape::kKSlots], ring.v[t % Shape::kVSlots], kb, b, crank, T, tid,
                                Shape::kThreads);
   };
-  // Steady-state MFMA phase.  Both products run unconditionally (a wave with
-  // no visible key in a tile gets P = 0 from its vector phase), so the loop
-  // has one path and the O accumulators stay in place.
+  // Steady-state MFMA phase.  Both products run unconditionally, so the loop
+  // has one path and the O accumulators stay in place.  (d_head 128: a wave with
+  // no visible key in a tile gets P = 0 from its vector phase; a V row of such a
+  // tile that is not finite still makes the wave's rows NaN.)
   // The MFMA phase runs at raised wave priority (s_setprio, this wave only):
   // its SIMD also holds a wave of the other group in its vector phase, and
   // the matrix core is kept fed first (2-3% faster than equal priority).
@@ -648,7 +650,7 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   };
   auto valu_phase = [&](int t) {
     const int kb = plan.tile(t) * kBN;
-    if (wave_dead(kb)) {
+    if (D == 128 && wave_dead(kb)) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -693,10 +695,6 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
   barrier();
 
-  qk_part(0);
-  if (grp == 1) sync_tile(0);
-  valu_phase(0);
-  if (grp == 0) sync_tile(0);
   // Tile t uses slots t % kKSlots and t % kVSlots: the loop runs kUnroll tiles
   // per pass with each slot a compile-time constant (its operand addresses are
   // then immediate offsets), the remaining tiles with the slots computed.
@@ -707,13 +705,52 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
     valu_phase(t);
     if (grp == 0) sync_tile(t);
   };
-  int t = 1;
-  for (; t + Shape::kUnroll <= n; t += Shape::kUnroll) {
+  // Tiles t0 .. t1 - 1, t0 < t1 (S(t0) first, P.V of tile t1 - 1 last).
+  auto run_tiles = [&](int t0, int t1) {
+    qk_part(t0 % Shape::kKSlots);
+    if (grp == 1) sync_tile(t0);
+    valu_phase(t0);
+    if (grp == 0) sync_tile(t0);
+    int t = t0 + 1;
+    if (D == 64)
+      for (; t < t1 && t % Shape::kUnroll != 1; ++t) tile_step(t, t % Shape::kUnroll);
+    for (; t + Shape::kUnroll <= t1; t += Shape::kUnroll) {
 #pragma unroll
-    for (int u = 0; u < Shape::kUnroll; ++u) tile_step(t + u, (u + 1) % Shape::kUnroll);
+      for (int u = 0; u < Shape::kUnroll; ++u) tile_step(t + u, (u + 1) % Shape::kUnroll);
+    }
+    for (; t < t1; ++t) tile_step(t, t % Shape::kUnroll);
+    pv_part((t1 - 1) % Shape::kVSlots);
+  };
+  if constexpr (D == 128) {
+    run_tiles(0, n);
+  } else {
+    // A wave takes part in the barriers and loads of every tile and skips the
+    // products of tiles in which none of its rows sees a key, so that a V that
+    // is not finite reaches only waves (32 rows) with a visible key in its tile
+    // (with P = 0 for the others it would make them 0 x V = NaN).  The tiles left
+    // are at most two runs: the sink's [0, head), then [band, end) from the
+    // band's first visible tile to the diagonal.
+    const int end = min(n, plan.n_sink_tiles + (r0 + 31) / kBN - plan.band_first + 1);
+    int head = end, band = end;
+    if (STREAM) {
+      const int lo = max(lo_of(r0, a.chunk, a.window), 0) / kBN;  // >= band_first
+      head = min(end, (a.n_sink + kBN - 1) / kBN);
+      band = plan.n_sink_tiles + lo - plan.band_first;
+      if (band <= head) head = end;
+    }
+    int t = 0;
+#pragma unroll 1
+    for (int seg = 0; seg < (STREAM ? 2 : 1); ++seg) {
+      const int t1 = seg == 0 ? head : end;
+      if (seg == 1)
+        for (; t < min(band, n); ++t) sync_tile(t);
+      if (t < t1) {
+        run_tiles(t, t1);
+        t = t1;
+      }
+    }
+    for (; t < n; ++t) sync_tile(t);
   }
-  for (; t < n; ++t) tile_step(t, t % Shape::kUnroll);
-  pv_part((n - 1) % Shape::kVSlots);
   // every wave passed the barrier of tile n-1 after its loads of the last
   // tiles completed, so the ring holds them
   if (APPEND && writer)

@@ -8,7 +8,8 @@ import pytest
 import torch
 
 import synth
-from paper_2608_06849_amd import PagedCache, RingCache, aoh_kv_append, aoh_prefill_append, aoh_prefill_varlen
+from paper_2608_06849_amd import (PagedCache, RingCache, aoh_kv_append, aoh_prefill, aoh_prefill_append,
+                                  aoh_prefill_chunked, aoh_prefill_varlen)
 from tests.helpers import BF16_MAX_ABS, BF16_MEAN_ABS, bits, to_dtype
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +97,28 @@ def test_packed(d, lens):
                       WINDOW)
     for a, b in ((full.k, full2.k), (full.v, full2.v), (ring.k, ring2.k), (ring.v, ring2.v)):
         assert np.array_equal(bits(a), bits(b)), f"{lens}: caches"
+
+
+@pytest.mark.parametrize("chunk", [0, 100])
+@pytest.mark.parametrize("at", [3, 70, 140, 255, 299])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_width_64_value_not_finite(bad, at, chunk):
+    # d_head 64: a V row that is not finite reaches the rows that see its key, and of the others only those in a
+    # wavefront (32 rows) with a row that sees a key of its tile (64 keys)
+    t, d = 300, 64
+    q, k, v = inputs(t, d, at)
+    v[at] = 0
+    want = aoh_prefill_chunked(q[None], k[None], v[None], MASK, N_SINK, WINDOW, chunk)[0] if chunk else \
+        aoh_prefill(q[None], k[None], v[None], MASK, N_SINK, WINDOW)[0]
+    v[at] = bad
+    got = aoh_prefill_chunked(q[None], k[None], v[None], MASK, N_SINK, WINDOW, chunk)[0] if chunk else \
+        aoh_prefill(q[None], k[None], v[None], MASK, N_SINK, WINDOW)[0]
+    i = torch.arange(t, device=DEV).view(-1, 1)
+    j = torch.arange(t, device=DEV).view(1, -1)
+    lo = (i // chunk) * chunk - WINDOW if chunk else i - WINDOW + 1
+    tile = slice(at // 64 * 64, at // 64 * 64 + 64)
+    for h in range(HQ):
+        sees = (j <= i) & ((j < N_SINK) | (j >= lo)) if MASK[h // (HQ // len(MASK))] else j <= i
+        assert not torch.isfinite(got[:, h][sees[:, at]].float()).any(), f"head {h}"
+        rows = torch.cat([sees[r:r + 32, tile].any().expand(min(32, t - r)) for r in range(0, t, 32)])
+        assert np.array_equal(bits(got[:, h][~rows]), bits(want[:, h][~rows])), f"head {h}"
