@@ -236,8 +236,8 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
   if ((st = schedule_heads(head_is_streaming, (int)Hkv, &hs))) return st;
   const int gs = (int)(Hq / Hkv);
   const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed);
-  const int64_t n_qblocks = ceil_div(T, rows);
-  if (n_qblocks * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
+  if (ceil_div(T, rows) * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
+  const int64_t n_qblocks = ceil_div(std::min(T, n_rows), rows);  // no sequence is longer than all rows
   if (append) {
     if ((st = check_paged(kv_full, hs.n_ret, B))) return st;
     if ((st = check_v_dim_major(kv_full, hs.n_ret, "a prefill that fills the caches"))) return st;
@@ -298,18 +298,48 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
       as.n_cache = hs.n_str; as.ring_blocks = (int)ceil_div(kv_ring->capacity, kPageTokens);
     }
   }
-  if (hs.n_ret && hs.n_str && prefill_mixed_preferred(ar, dt, (int)D, rows)) {
-    // One launch, retrieval items first: their causal work dominates
-    // (O(T^2) vs O(T(n_sink+window))); the streaming items fill the tail.
-    hipError_t e = launch_prefill_mixed(ar, as, out_f32, (int)D, rows, s);
-    if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
-  } else {
+  // The runtime takes a launch's work-items modulo 2^32: a larger grid runs in
+  // part, without an error (a packed batch gets there with a loose max_seqlen,
+  // in one launch for both head types: 513 sequences, 32 heads of width 64,
+  // 131072).  The query blocks of a launch stay below half of that, which leaves
+  // room for the dynamic tail's spare workgroups; larger batches go in parts.
+  const int64_t seq_items = n_qblocks * Hq * (dt == AOH_BF16 ? 2 * rows : rows);
+  const int64_t part = std::max<int64_t>(1, (1ll << 31) / seq_items);
+  for (int64_t b0 = 0; b0 < B; b0 += part) {
+    PrefillArgs pr = ar, ps = as;
+    for (PrefillArgs* p : {&pr, &ps}) {
+      p->B = (int)std::min(part, B - b0);
+      const int es = elt_size(dt);
+      if (packed) {
+        p->cu_seqlens += b0;
+      } else {
+        p->q = static_cast<const char*>(a.q) + b0 * a.q_sb * es;
+        p->k = static_cast<const char*>(a.k) + b0 * a.k_sb * es;
+        p->v = static_cast<const char*>(a.v) + b0 * a.v_sb * es;
+        p->out = static_cast<char*>(a.out) + b0 * a.o_sb * elt_size(out->dtype);
+      }
+      if (!p->append) continue;
+      if (p->block_table) {
+        p->block_table += b0 * p->max_pages;
+      } else {
+        const int64_t at = b0 * p->n_cache * p->ring_blocks * kPageTokens * D * es;
+        p->ck = static_cast<char*>(p->ck) + at;
+        p->cv = static_cast<char*>(p->cv) + at;
+      }
+    }
+    if (hs.n_ret && hs.n_str && prefill_mixed_preferred(pr, dt, (int)D, rows)) {
+      // One launch, retrieval items first: their causal work dominates
+      // (O(T^2) vs O(T(n_sink+window))); the streaming items fill the tail.
+      hipError_t e = launch_prefill_mixed(pr, ps, out_f32, (int)D, rows, s);
+      if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
+      continue;
+    }
     if (hs.n_ret) {
-      hipError_t e = launch_prefill(ar, dt, out_f32, (int)D, rows, false, s);
+      hipError_t e = launch_prefill(pr, dt, out_f32, (int)D, rows, false, s);
       if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill retrieval launch: %s", hipGetErrorString(e));
     }
     if (hs.n_str) {
-      hipError_t e = launch_prefill(as, dt, out_f32, (int)D, rows, true, s);
+      hipError_t e = launch_prefill(ps, dt, out_f32, (int)D, rows, true, s);
       if (e != hipSuccess) return fail(AOH_ERR_HIP, "prefill streaming launch: %s", hipGetErrorString(e));
     }
   }

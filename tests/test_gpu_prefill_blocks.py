@@ -122,3 +122,34 @@ def test_width_64_value_not_finite(bad, at, chunk):
         assert not torch.isfinite(got[:, h][sees[:, at]].float()).any(), f"head {h}"
         rows = torch.cat([sees[r:r + 32, tile].any().expand(min(32, t - r)) for r in range(0, t, 32)])
         assert np.array_equal(bits(got[:, h][~rows]), bits(want[:, h][~rows])), f"head {h}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_grids_of_2_32_work_items(d):
+    # blocks of the longest prompt x sequences x heads, with a bound on the length that is far from the real ones:
+    # more work-items than a launch can hold
+    b, hq = 1024, 32
+    lens = [(37 * i) % 130 + 1 for i in range(b)]
+    total = sum(lens)
+    assert (total // 128) * b * hq * 256 > 1 << 32
+    g = torch.Generator(device=DEV).manual_seed(d)
+    x = torch.randn((total, hq + 2, d), dtype=torch.bfloat16, device=DEV, generator=g)
+    q, k, v = x[:, :hq], x[:, hq:hq + 1], x[:, hq + 1:]
+    k, v = torch.cat([k, v], 1), torch.cat([v, k], 1)
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=DEV)
+    got = []
+    for bound in (max(lens), 131072):
+        full, ring = caches(b, max(lens), d, d)
+        out = torch.full_like(q, float("nan"))
+        aoh_prefill_varlen(q, k, v, cu, bound, MASK, N_SINK, WINDOW, kv_full=full, kv_ring=ring, out=out)
+        got.append([out, full.k, full.v, ring.k, ring.v])
+    for a, w in zip(*got):
+        assert np.array_equal(bits(a), bits(w))
+
+
+def test_dense_batch_of_2_31_work_items():
+    # one token each: the output is its V
+    b, hq = 300000, 32
+    x = torch.randn((b, 1, hq + 4, 64), dtype=torch.bfloat16, device=DEV)
+    out = aoh_prefill(x[:, :, :hq], x[:, :, hq:hq + 2], x[:, :, hq + 2:], MASK, N_SINK, WINDOW)
+    assert torch.equal(out, x[:, :, hq + 2:].repeat_interleave(hq // 2, 2))
