@@ -20,6 +20,8 @@
 // lane-local and lets the V^T operand be one 16-byte load from the
 // dimension-major V page ([D][16] per page).  K rows are read with 16-byte
 // loads covering 64 contiguous bytes per token row per instruction.
+#include <cfloat>
+
 #include "aoh_device.h"
 #include "aoh_internal.h"
 
@@ -112,7 +114,7 @@ __device__ __forceinline__ void fold_chunk(const DecodeArgs& a, const u32x4 (&kc
       if ((G & 1) == 0) buf.refs[at] = top * (1.f / kScoreCodeScale);
     }
   }
-  const float m_new = fmaxf(m_run, mx);  // finite: every chunk holds a valid token
+  const float m_new = fmaxf(m_run, mx);
   const float alpha = fast_exp2(m_run - m_new);
   m_run = m_new;
   bf16x8 pop;
@@ -229,7 +231,10 @@ __device__ __forceinline__ void decode_split_body(const DecodeArgs& a, const Cac
       vreg[nb] = ld16_stream(vc + vb + (int64_t)(16 * nb + (lane & 15)) * kPage + v_off);
   };
 
-  float m_run = -INFINITY;
+  // Finite, so that tokens whose score is -inf (a K that is not finite) have
+  // weight 0 however the range is cut: exp2(-inf - m) is 0, with a chunk of such
+  // tokens first and m = -inf it would be NaN.
+  float m_run = -FLT_MAX;
   float l_run = 0.f;
 
   if (APPEND) {

@@ -66,3 +66,22 @@ def test_sequences_without_tokens():
     before = [bits(c) for c in (run.full.k, run.ring.k)]
     aoh_decode_step(q, new, new, run.full, run.ring, run.mask, torch.zeros_like(lens), 4, 60, workspace=run.ws)
     assert all(np.array_equal(bits(c), w) for c, w in zip((run.full.k, run.ring.k), before))
+
+
+@pytest.mark.parametrize("B,D", [(2, 128), (3, 64), (64, 128), (130, 64), (1030, 64)])
+@pytest.mark.parametrize("first,n", [(0, 16), (0, 48), (16, 16), (48, 32), (5, 90)])
+def test_scores_of_minus_infinity(B, D, first, n):
+    # a K of -inf in a dimension where q is positive: weight 0 for these tokens, on every path and wherever their
+    # blocks lie in a wavefront's range; the same bits as for a K so low that the weight underflows
+    Hq, Hkv, mask = 8, 2, [0, 1]
+    lens = torch.tensor([100 + 37 * i % 150 for i in range(B)], dtype=torch.int32, device=DEV)
+    outs = []
+    for low in (-3e4, -float("inf")):
+        run = Run(B, Hq, Hkv, D, mask, 4, 300, lens.tolist(), 1, torch.bfloat16, seed=B + n)
+        run.k_seq[:, first:first + n, :, 0] = low
+        run.append_prompts()
+        q = run.q_steps[0].to(DEV)
+        q[..., 0] = 1.0
+        outs.append(aoh_decode(q, run.full, run.ring, mask, run.lens, 4, 300, workspace=run.ws))
+    assert torch.isfinite(outs[1].float()).all()
+    assert np.array_equal(bits(outs[0]), bits(outs[1]))
