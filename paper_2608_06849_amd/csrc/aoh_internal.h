@@ -46,6 +46,7 @@ struct PrefillArgs {
   int32_t n_cache;              // KV heads stored in the cache
   int32_t ring_blocks;          // ring only: Cpad / 16
   uint8_t kv_heads[kMaxKvHeads];
+  int32_t part;          // 128 rows, not seq_major: sequences whose blocks are visited together
 };
 
 // One cache type as seen by the decode split pass.  Work item = (batch, KV
@@ -196,6 +197,8 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, i
                           hipStream_t s);
 // Query rows per workgroup for n_rows tokens in `batch` sequences; PrefillArgs::n_qblocks counts blocks of them.
 int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed);
+// PrefillArgs::part for sequences of avg_len tokens.
+int prefill_part(int rows, int d, int64_t avg_len, int n_kv, int gs, int batch);
 // One launch for a layer with both head types (bf16; d_head 64, or short
 // retrieval launches; see prefill.hip).
 bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d, int rows);

@@ -29,7 +29,9 @@
 //
 // fp32 kernel: a plain per-row kernel (one thread per query row) kept exact
 // for fp32 inputs; it has no performance role.
+#include <algorithm>
 #include <atomic>
+#include <numeric>
 #include <type_traits>
 
 #include "aoh_device.h"
@@ -238,20 +240,23 @@ constexpr int wait_vm(int n) { return n | (0x7 << 4) | (0xF << 8); }  // n < 16
 constexpr int kWaitLgkm0 = 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14);
 
 
-// Work item of a workgroup: query block qb (rows
-// qb * rows ..), local query head qh_local of the launch's KV-head list and
-// sequence b.  Dense batches use the XCD-aware order below; packed batches
+// Work item of a workgroup: query block qb (rows qb * ROWS ..), local query
+// head qh_local of the launch's KV-head list and sequence b.  Dense batches use the XCD-aware order below; packed batches
 // with sequence-major order walk cu_seqlens.  Returns false when the
 // workgroup has no work (past the last sequence's blocks).
-__device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int rows, int wg, int& qb, int& qh_local,
-                                             int& b) {
+template <int ROWS>
+__device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int wg, int& qb, int& qh_local, int& b) {
   const int n_qh = a.n_kv * a.gs;
-  const int per_block = n_qh * a.B;
-  qb = a.n_qblocks - 1 - wg / per_block;
-  const int rem = wg % per_block;
-  qh_local = rem % n_qh;
-  b = rem / n_qh;
   if (!a.seq_major) {
+    int b0 = 0, B = a.B;
+    if constexpr (ROWS == 128) {
+      // Parts of the batch one after the other (PrefillArgs::part), each in the
+      // order below.
+      const int per_part = a.n_qblocks * n_qh * a.part;
+      b0 = wg / per_part * a.part;
+      B = min(a.part, a.B - b0);
+      wg %= per_part;
+    }
     // XCD-aware order.  Workgroups go to the 8 XCDs (each with its own L2)
     // in turn; work item group j = (query block, sequence, KV head), heaviest
     // block first, holds the gs query heads that read the same K/V tiles.
@@ -264,9 +269,9 @@ __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int rows, int
     // keeps serving one (sequence, KV head), whose causal prefix stays in its
     // L2.  The trailing groups that do not fill a round of 8 are dealt in
     // plain order.
-    const int n_groups = a.n_qblocks * a.n_kv * a.B;
+    const int n_groups = a.n_qblocks * a.n_kv * B;
     const int full = 8 * a.gs * (n_groups / 8);
-    const int pq = a.n_kv * a.B;
+    const int pq = a.n_kv * B;
     int j, hl;
     if (wg < full) {
       const int slot = wg >> 3;
@@ -279,10 +284,9 @@ __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int rows, int
       j = (full / a.gs) + (wg - full) / a.gs;
       hl = (wg - full) % a.gs;
     }
-    const int per_qb = a.n_kv * a.B;
-    qb = a.n_qblocks - 1 - j / per_qb;
-    const int r2 = j % per_qb;
-    b = r2 / a.n_kv;
+    qb = a.n_qblocks - 1 - j / pq;
+    const int r2 = j % pq;
+    b = b0 + r2 / a.n_kv;
     qh_local = (r2 % a.n_kv) * a.gs + hl;
   }
   if (a.seq_major) {
@@ -292,7 +296,7 @@ __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int rows, int
     for (int s2 = 0; s2 < a.B; ++s2) {
       const int s0 = min(max(a.cu_seqlens[s2], 0), a.total);
       const int s1 = min(max(a.cu_seqlens[s2 + 1], s0), a.total);
-      const int nb = (min(s1 - s0, a.T) + rows - 1) / rows;
+      const int nb = (min(s1 - s0, a.T) + ROWS - 1) / ROWS;
       if (unit < nb) {
         b = s2;
         qb = nb - 1 - unit;
@@ -375,7 +379,7 @@ __device__ __forceinline__ void prefill_pp_body(const PrefillArgs& a, int wg, PP
   constexpr int kMBlocks = D / 32;
 
   int qb, qh_local, b;
-  if (!pp_work_item(a, ROWS, wg, qb, qh_local, b)) return;
+  if (!pp_work_item<ROWS>(a, wg, qb, qh_local, b)) return;
   const int g = a.kv_heads[qh_local / a.gs];
   const int h = g * a.gs + (qh_local % a.gs);
 
@@ -981,6 +985,26 @@ int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longes
   if (d == 64) return 128;
   if (!packed) return longest <= 8192 ? 128 : 256;
   return n_rows <= batch * (batch >= 8 ? 16384 : 8192) ? 128 : 256;
+}
+
+// The blocks of a batch whose K/V exceed the 256 MB cache in front of HBM would
+// fetch them from HBM again for each query block if all sequences were visited
+// together: with 128 rows and one query head a KV head that is more than HBM
+// gives.  The sequences are therefore visited in parts of at most kPartBytes
+// (one head a group; four times that otherwise, where L2 serves the group's
+// heads and short parts cost balance), rounded up to whole rounds of the XCD
+// order.  32 heads of width 128, one a group: 16 x 4096 tokens 2.14 ms, 3.67 all
+// together, 16 x 2048 0.62 (1.01), 128 x 256, half of them streaming, 309 us (449);
+// 128 MB parts 2.23 ms, 0.65 and 430.  Two a group, 32 x 4096: 4.44 ms (5.21).
+// 256 rows halve the fetches and keep the order their work queues assume.
+constexpr int64_t kPartBytes = 32 << 20;
+
+int prefill_part(int rows, int d, int64_t avg_len, int n_kv, int gs, int batch) {
+  if (rows != 128 || n_kv < 1) return batch;
+  const int64_t seq_bytes = std::max<int64_t>(1, avg_len * n_kv * d * 4);
+  const int64_t fit = std::max<int64_t>(1, kPartBytes * (gs == 1 ? 1 : 4) / seq_bytes);
+  const int64_t whole = 8 / std::gcd(n_kv, 8);
+  return (int)std::min<int64_t>(batch, (fit + whole - 1) / whole * whole);
 }
 
 hipError_t launch_prefill_mixed(const PrefillArgs& ar, const PrefillArgs& as, int out_f32, int d, int rows,

@@ -153,3 +153,45 @@ def test_dense_batch_of_2_31_work_items():
     x = torch.randn((b, 1, hq + 4, 64), dtype=torch.bfloat16, device=DEV)
     out = aoh_prefill(x[:, :, :hq], x[:, :, hq:hq + 2], x[:, :, hq + 2:], MASK, N_SINK, WINDOW)
     assert torch.equal(out, x[:, :, hq + 2:].repeat_interleave(hq // 2, 2))
+
+
+@pytest.mark.parametrize("b,hq,mask,d", [
+    (34, 32, [0] * 32, 128),             # parts of 14 sequences: two whole ones and a rest
+    (34, 32, [0, 1] * 16, 64),           # both types, up to 58 sequences a part: all in one
+    (100, 13, [0] * 10 + [1] * 3, 128),  # parts of 48: rounded up to whole rounds of 8 (sequence, head) pairs
+    (70, 64, [0, 0, 1, 0] * 8, 128),     # two query heads a group: parts of 36 and all in one
+])
+@pytest.mark.parametrize("packed", [False, True])
+def test_batches_in_parts(b, hq, mask, d, packed):
+    # more K/V than a part of the batch holds: each sequence as by itself, bit for bit, and its rows of the caches
+    n_kv = len(mask)
+    lens = [150 + 7 * (i % 40) % 150 for i in range(b)] if packed else [140 if hq < 64 else 300] * b
+    total = sum(lens)
+    g = torch.Generator(device=DEV).manual_seed(b + hq)
+    q, k, v = (torch.randn((total, h, d), dtype=torch.bfloat16, device=DEV, generator=g) for h in (hq, n_kv, n_kv))
+    at = np.cumsum([0] + lens)
+    pages = (max(lens) + 15) // 16
+    table = torch.from_numpy(synth.page_permutation(b * pages, b).reshape(b, pages).copy())
+    got = []
+    for _ in range(2):
+        full = PagedCache.allocate(b * pages, mask.count(0), d, torch.bfloat16, table)
+        ring = RingCache.allocate(b, max(sum(mask), 1), N_SINK, WINDOW, d, torch.bfloat16)
+        for c in (full, ring):
+            c.k.zero_()
+            c.v.zero_()
+        got.append([torch.full_like(q, float("nan")), full, ring])
+    ring_of = lambda r: r if sum(mask) else None  # noqa: E731
+    out, full, ring = got[0]
+    if packed:
+        cu = torch.tensor(at, dtype=torch.int32, device=DEV)
+        aoh_prefill_varlen(q, k, v, cu, max(lens), mask, N_SINK, WINDOW, kv_full=full, kv_ring=ring_of(ring), out=out)
+    else:
+        x = [t.view(b, lens[0], -1, d) for t in (q, k, v, out)]
+        aoh_prefill_append(x[0], x[1], x[2], mask, N_SINK, WINDOW, full, ring_of(ring), out=x[3])
+    want, full2, ring2 = got[1]
+    for i in range(b):
+        s = slice(at[i], at[i + 1])
+        aoh_prefill_append(q[None, s], k[None, s], v[None, s], mask, N_SINK, WINDOW, full2.rows(i, i + 1),
+                           ring_of(RingCache(ring2.k[i:i + 1], ring2.v[i:i + 1], ring2.capacity)), out=want[None, s])
+    for a, w in zip((out, full.k, full.v, ring.k, ring.v), (want, full2.k, full2.v, ring2.k, ring2.v)):
+        assert np.array_equal(bits(a), bits(w))
