@@ -235,7 +235,7 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
   HeadSchedule hs;
   if ((st = schedule_heads(head_is_streaming, (int)Hkv, &hs))) return st;
   const int gs = (int)(Hq / Hkv);
-  const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed);
+  const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed, hs.n_ret, hs.n_str);
   if (ceil_div(T, rows) * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
   const int64_t n_qblocks = ceil_div(std::min(T, n_rows), rows);  // no sequence is longer than all rows
   if (append) {

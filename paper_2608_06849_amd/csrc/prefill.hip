@@ -976,15 +976,22 @@ static hipError_t launch_mixed_d(const PrefillArgs& ar, const PrefillArgs& as, i
 // pays: 32 query / 8 KV heads, half of them streaming, 4 x 4000 tokens 220 us;
 // 250 with 256 rows, 259 with 384 rows of 12 waves).  d_head 128: 256 rows where
 // prompts are long (a K/V tile is fetched for twice the rows: 32768 tokens 3.87
-// ms, 4.15 with 128), 128 where items are few or uneven: one prompt of 701 tokens
-// 28.6 against 36.6 us, 4 x 4000 388 against 398, 8192 tokens even, 16 packed
-// prompts of 512-24576 tokens 13.2 against 13.7 ms, 12 of 500-9000 1.81 against
-// 1.99; 4 packed of 8000-24000 4.38 against 4.33.
-int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed) {
+// ms, 4.15 with 128), 128 where items are few or uneven, or many of them
+// streaming (whose blocks of 256 rows visit more tiles outside a row's window).
+// The line is on the prompts' length, earlier where more than two thirds of the
+// KV heads are retrieval; 128 / 256 rows, 32 query heads of 8 KV heads: one
+// prompt of 2048 tokens, none streaming, 50 / 53 us, 6000 even, 8192 482 / 469;
+// 4 x 8192, 4 streaming, 1.16 / 1.18 ms, 8 x 12000 4.86 / 4.75, 2 x 12000 even.
+// 8 or more prompts whose mean is below two thirds of the longest leave more
+// to balance: 16 of 512-24576 tokens 13.2 / 13.7 ms, 16 of 4100-15700, none
+// streaming, 8.36 / 8.55.
+int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed, int n_ret, int n_str) {
   if (dtype == 1) return kPrefillRowsF32;
   if (d == 64) return 128;
-  if (!packed) return longest <= 8192 ? 128 : 256;
-  return n_rows <= batch * (batch >= 8 ? 16384 : 8192) ? 128 : 256;
+  const bool causal = 2 * n_str < n_ret;
+  const int64_t even = causal ? 6144 : 8192, uneven = causal ? 10240 : 16384;
+  if (!packed) return longest <= even ? 128 : 256;
+  return n_rows <= batch * (batch >= 8 && 2 * longest * batch > 3 * n_rows ? uneven : even) ? 128 : 256;
 }
 
 // The blocks of a batch whose K/V exceed the 256 MB cache in front of HBM would

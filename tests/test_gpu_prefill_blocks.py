@@ -17,7 +17,7 @@ DEV = "cuda"
 HQ, MASK, N_SINK, WINDOW = 4, [0, 1], 20, 150
 
 
-def reference(q, k, v, chunk):
+def reference(q, k, v, chunk, mask=MASK):
     """[T, H, D] bf16 -> [T, Hq, D] fp32."""
     t = q.shape[0]
     i = torch.arange(t, device=q.device).view(-1, 1)
@@ -28,7 +28,7 @@ def reference(q, k, v, chunk):
     for h in range(HQ):
         g = h // (HQ // len(MASK))
         s = q[:, h].float() @ k[:, g].float().t().contiguous() / q.shape[-1] ** 0.5
-        out[:, h] = torch.softmax(s.masked_fill(~masks[MASK[g]], -torch.inf), -1) @ v[:, g].float()
+        out[:, h] = torch.softmax(s.masked_fill(~masks[mask[g]], -torch.inf), -1) @ v[:, g].float()
     return out
 
 
@@ -75,6 +75,18 @@ def test_long_prompt(t):
     full, ring = caches(1, t, 128, t)
     out = aoh_prefill_append(q[None], k[None], v[None], MASK, N_SINK, WINDOW, full, ring)
     check(out[0], reference(q, k, v, 0), f"T {t}")
+
+
+@pytest.mark.parametrize("lens", [[6144], [6145], [6145, 6145], [9000, 1, 257, 64, 65, 128, 700, 31], [9000] * 8])
+def test_long_prompts_retrieval_only(lens):
+    # the change from 128 to 256 rows of a layer without streaming heads: single, packed, uneven and even prompts
+    q, k, v = inputs(sum(lens), 128, sum(lens))
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=DEV)
+    out = aoh_prefill_varlen(q, k, v, cu, max(lens), [0, 0], N_SINK, WINDOW) if len(lens) > 1 else \
+        aoh_prefill(q[None], k[None], v[None], [0, 0], N_SINK, WINDOW)[0]
+    for i in range(len(lens)):
+        s = slice(int(cu[i]), int(cu[i + 1]))
+        check(out[s], reference(q[s], k[s], v[s], 0, [0, 0]), f"{lens} sequence {i}")
 
 
 @pytest.mark.parametrize("d,lens", [
