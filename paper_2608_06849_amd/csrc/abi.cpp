@@ -170,6 +170,44 @@ size_t workspace_bytes(int batch, int hq, int d, const SplitPlan& p) {
   return std::max(fixed, ws);
 }
 
+// Split pass of a decode step: fixed splits from the cache capacity, or the
+// step's work space split on the device (two workgroups per CU), which follows
+// any mix of lengths and of cache types, by the kernel whose plan is in registers
+// or, for many items (sequence, KV head) and for more sequences than that one
+// takes, by the one that holds whole items.
+enum class DecodeKernel { kFixed, kWorkSpace, kMany };
+
+size_t many_rows(int cu, int gs) { return (size_t)4 * cu * gs; }
+
+// kMany saves barriers and partials at every item, which weigh the more the
+// larger a group is, but an item that it cuts over many workgroups it merges in
+// one: it is taken from so many items on that it is not slower where lengths
+// differ a lot either.  kMany / kWorkSpace, us a layer of d_head 128, half of its
+// heads streaming: 128 items of one head a group, 303-4209 tokens 23.9 / 21.4,
+// 203-8710 29.0 / 24.1, 384 of 344-5900 47.2 / 47.7; 128 of two, 488-5902 28.4 /
+// 26.4, 256 of 411-5859 39.7 / 42.1; 128 of four, 200-359 14.9 / 18.9, 323-5092
+// 25.3 / 25.4, 232-9560 34.6 / 35.4, 313-15527 43.6 / 42.1, 256 of 307-5546 38.4 /
+// 45.5.  d_head 64, 256 items of 300-6000: of four heads 0.92 of the time, of two
+// 0.97-1.03, of one 1.07, 512 of one 0.96-1.  With short sequences (a capacity of
+// kManyShortBlocks) no item is in many workgroups.  Anchor steps cross in the same
+// places (128 items of four 0.75-1.02 of the other's time, 256 0.72-0.92).
+//
+// Above kWsMaxBatch sequences kMany is taken wherever its slots fit in the
+// workspace, whose size is that of the fixed splits: batch x KV heads x (splits
+// an item) above 4 x CUs, e.g. 65 sequences of one KV head from 481 tokens of
+// capacity on.  Below that, an item's fixed splits are one or a few workgroups.
+constexpr int kManyShortBlocks = 32;
+
+DecodeKernel decode_kernel(int64_t B, int64_t Hkv, int gs, int D, int64_t blocks, int cu, size_t workspace) {
+  const int64_t items = B * Hkv;
+  int64_t many = D == 128 ? 128 : 256;
+  if (blocks > kManyShortBlocks) many = D == 128 ? (gs == 1 ? 384 : gs < 4 ? 192 : 128) : (gs == 1 ? 512 : gs < 4 ? 384 : 256);
+  const size_t need = many_rows(cu, gs) * (D + 2) * sizeof(float) + 16 + 8 * cu * sizeof(int32_t);
+  if ((B > kWsMaxBatch || items >= many) && B <= kManyMaxBatch && items * (blocks + 16) < (1ll << 29) && need <= workspace)
+    return DecodeKernel::kMany;
+  return B <= kWsMaxBatch && items * blocks < (1ll << 30) ? DecodeKernel::kWorkSpace : DecodeKernel::kFixed;
+}
+
 }  // namespace
 
 extern "C" {
@@ -494,6 +532,16 @@ aoh_status aoh_kv_append(const aoh_tensor* k_new, const aoh_tensor* v_new,
   return ok();
 }
 
+// For the tests (not part of aoh.h): the DecodeKernel of a plain, anchor or fused
+// bf16 step on 256 CUs.
+int32_t aoh_internal_decode_kernel(int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int32_t d_head,
+                                   int32_t max_pages, int32_t ring_capacity) {
+  const SplitPlan p = plan_splits(batch, max_pages, ring_capacity, 0, 1);
+  return (int32_t)decode_kernel(batch, n_kv_heads, n_q_heads / n_kv_heads, d_head,
+                                std::max(max_pages, p.ring_blocks), kWsMaxWgs / 2,
+                                workspace_bytes(batch, n_q_heads, d_head, p));
+}
+
 size_t aoh_decode_workspace_bytes(int32_t batch, int32_t n_q_heads, int32_t d_head,
                                   int32_t max_pages_per_seq, int32_t ring_capacity) {
   if (batch < 1 || n_q_heads < 1 || (d_head != 64 && d_head != 128) || max_pages_per_seq < 1 ||
@@ -698,33 +746,20 @@ static aoh_status decode_impl(const aoh_tensor* q, const aoh_paged_cache* kv_ful
     return ok();
   }
 
-  // Plain, anchor and fused steps split the step's work space on the device
-  // (two workgroups per CU), which follows any mix of lengths and of cache
-  // types.  Many items, or more sequences than the other takes, go to the kernel
-  // that holds whole items, else it is the one whose plan is in registers.
-  // 128 items of d_head 128, 256 of 64, are where the first is never slower (us
-  // a call, first / second): 128 items of 200-2000 tokens 23.3 / 26.9, of
-  // 2K-32K 108.1 / 108.8, 64 items of 4000 tokens 27.8 / 26.0; d_head 64: 128
-  // items of 2K-32K 59.6 / 57.0, 192 of 2K-16K 51.7 / 52.2, 256 of 200-8000
-  // 38.4 / 42.9.  Larger batches, many sequences of a page or two (whose fixed
-  // splits are one workgroup an item and whose workspace is too small) and the
-  // reuse layer take fixed splits from the capacity.
   const int64_t ws_blocks = std::max<int64_t>(max_pages, sp.ring_blocks);
   const int cu = std::min(compute_units(), kWsMaxWgs / 2);
   size_t part_rows = (size_t)B * Hq * sp_bound.max_splits;
-  if (x.mode != kReuse) {
-    const size_t many_rows = (size_t)4 * cu * gs;
-    if ((B > kWsMaxBatch || B * Hkv * D >= 128 * 128) && B <= kManyMaxBatch && B * Hkv * (ws_blocks + 16) < (1ll << 29) &&
-        many_rows * (D + 2) * sizeof(float) + 16 + 8 * cu * sizeof(int32_t) <= base_need) {
-      a.many_wgs = 2 * cu;
-      a.ws_cu = cu;
-      part_rows = many_rows;
-      a.out = out->data; a.o_sb = out->stride[0]; a.o_sh = out->stride[1];
-      a.out_f32 = out->dtype == AOH_F32;
-    } else if (B <= kWsMaxBatch && B * Hkv * ws_blocks < (1ll << 30)) {
-      a.ws_cu = cu;
-      part_rows = (size_t)(2 * cu + B * Hkv) * gs;
-    }
+  const DecodeKernel kernel =
+      x.mode == kReuse ? DecodeKernel::kFixed : decode_kernel(B, Hkv, gs, (int)D, ws_blocks, cu, base_need);
+  if (kernel == DecodeKernel::kMany) {
+    a.many_wgs = 2 * cu;
+    a.ws_cu = cu;
+    part_rows = many_rows(cu, gs);
+    a.out = out->data; a.o_sb = out->stride[0]; a.o_sh = out->stride[1];
+    a.out_f32 = out->dtype == AOH_F32;
+  } else if (kernel == DecodeKernel::kWorkSpace) {
+    a.ws_cu = cu;
+    part_rows = (size_t)(2 * cu + B * Hkv) * gs;
   }
   float* part_acc = reinterpret_cast<float*>(workspace);
   float* part_ml = part_acc + part_rows * D;

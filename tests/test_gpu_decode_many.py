@@ -1,7 +1,7 @@
 """Decode steps of many (sequence, KV head) items on the GPU, against the oracle (Sec. 5, Eq. 8).
 
-From 128 items of d_head 128 (256 of 64) on, or 65 sequences, the split pass holds whole items per wavefront or
-workgroup and merges only what crosses workgroups.  The cases put items on both sides of a wavefront's, a workgroup's
+From so many items on (128 of d_head 128 and 256 of 64, more where groups are small and sequences long), or from 65
+sequences on, the split pass holds whole items per wavefront or workgroup and merges only what crosses workgroups.  The cases put items on both sides of a wavefront's, a workgroup's
 and many workgroups' range, and cover the sequence tables of one wavefront (256) and of four (1024), and the batches
 beyond them, which take fixed splits."""
 import numpy as np
@@ -22,10 +22,13 @@ CASES = [
     (64, 8, 2, 128, [1, 0], 4, 300, [(91 * i) % 700 + 1 for i in range(64)]),       # 128 items of width 128
     (66, 14, 2, 128, [0, 0], 8, 32, [9000] + [(7 * i) % 40 + 1 for i in range(65)]),  # one item over many workgroups
     (70, 4, 4, 64, [1, 1, 1, 1], 16, 100, [(29 * i) % 300 + 1 for i in range(70)]),  # rings only
-    (257, 2, 1, 64, [0], 4, 32, [(13 * i) % 60 + 1 for i in range(257)]),            # tables of four wavefronts
+    (257, 2, 1, 64, [0], 4, 32, [(13 * i) % 60 + 1 for i in range(257)]),            # too small a workspace: fixed splits
+    (257, 4, 4, 64, [0] * 4, 4, 32, [(13 * i) % 60 + 1 for i in range(257)]),        # tables of four wavefronts, one in use
+    (601, 4, 4, 64, [0, 1, 0, 1], 4, 28, [(13 * i) % 60 + 1 for i in range(601)]),   # three, the last quad not full
     (1024, 2, 2, 64, [0, 1], 2, 14, [i % 33 + 1 for i in range(1024)]),
     (1030, 2, 2, 64, [0, 1], 2, 14, [i % 33 + 1 for i in range(1030)]),              # beyond them
 ]
+SMALL_WORKSPACE = [(257, 2, 1)]  # rows of CASES that take fixed splits for it
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,mask,n_sink,window,prompt", CASES)
