@@ -18,6 +18,8 @@
 // threshold, and as many keys equal to it as still needed, lowest positions
 // first.  Sequences with at most k positions select all of them; unused
 // entries are -1.
+#include <type_traits>
+
 #include "aoh_device.h"
 #include "aoh_internal.h"
 
@@ -169,55 +171,69 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
   const int64_t group = ((int64_t)b * a.n_kv + blockIdx.y) * a.gs * a.score_len;
   const uint16_t* c0 = a.score_codes + group;  // [block][head][16]
   const float* r0 = a.score_refs + group / 16;  // [block][head]
-  // Eight consecutive positions (half a block: 16 bytes of codes a head) or four
-  // (16 bytes of keys) a thread (32 lists of 131000 positions: 15.6 and 8.0 us the
-  // two passes, 18.9 and 11.0 with one position a thread); segments start at multiples of 4096.  Codes past
-  // the segment's end lie in the padded row and are not used.
-  constexpr int kRun = PASS == 0 ? 8 : 4;
-  for (int j0 = v.seg0 + kRun * t; j0 < v.seg1; j0 += kRun * kTopkThreads) {
-    uint32_t key[kRun];
-    if (PASS == 0) {
-      // score = ref - code / kScoreCodeScale (log2 units): a grid point,
-      // computed exactly, so equal kept scores give equal keys
-      float p[kRun];
+  // RUN consecutive positions a thread; segments start at multiples of 4096, codes
+  // past the segment's end lie in the padded row and are not used.
+  auto visit = [&](auto run) {
+    constexpr int RUN = decltype(run)::value;
+    static_assert(RUN == 1 || RUN % 4 == 0, "keys leave in fours");
+    for (int j0 = v.seg0 + RUN * t; j0 < v.seg1; j0 += RUN * kTopkThreads) {
+      uint32_t key[RUN];
+      const bool whole = RUN > 1 && j0 + RUN <= v.seg1;
+      if (PASS == 0) {
+        // score = ref - code / kScoreCodeScale (log2 units): a grid point,
+        // computed exactly, so equal kept scores give equal keys
+        float p[RUN];
 #pragma unroll
-      for (int i = 0; i < kRun; ++i) p[i] = 0.f;
-      for (int h = 0; h < a.gs; ++h) {
-        const int64_t at = (int64_t)(j0 / 16) * a.gs + h;
-        const float ref = r0[at], m = s_m[h], il = s_il[h];
-        const u32x4 c = ld16(c0 + at * 16 + j0 % 16);
+        for (int i = 0; i < RUN; ++i) p[i] = 0.f;
+        for (int h = 0; h < a.gs; ++h) {
+          const int64_t at = (int64_t)(j0 / 16) * a.gs + h;
+          const float ref = r0[at], m = s_m[h], il = s_il[h];
+          uint16_t c[RUN];
+          __builtin_memcpy(c, __builtin_assume_aligned(c0 + at * 16 + j0 % 16, 2 * RUN), sizeof(c));
 #pragma unroll
-        for (int i = 0; i < kRun; ++i) {
-          const uint32_t code = (c[i / 2] >> (16 * (i % 2))) & 0xffffu;
-          const float xq = ref - (float)code * (1.f / kScoreCodeScale);
-          p[i] += fast_exp2(xq - m) * il;
+          for (int i = 0; i < RUN; ++i) {
+            const float xq = ref - (float)c[i] * (1.f / kScoreCodeScale);
+            p[i] += fast_exp2(xq - m) * il;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < RUN; ++i) key[i] = __builtin_bit_cast(uint32_t, p[i]) & kKeyMask;
+        if (whole) {
+#pragma unroll
+          for (int i = 0; i < RUN / 4; ++i)
+            st16(v.keys + j0 + 4 * i, u32x4{key[4 * i], key[4 * i + 1], key[4 * i + 2], key[4 * i + 3]});
+        } else {
+#pragma unroll
+          for (int i = 0; i < RUN; ++i)
+            if (j0 + i < v.seg1) v.keys[j0 + i] = key[i];
+        }
+      } else {
+        if (whole) {
+          const u32x4 w = ld16(v.keys + j0);
+#pragma unroll
+          for (int i = 0; i < RUN; ++i) key[i] = w[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < RUN; ++i) key[i] = j0 + i < v.seg1 ? v.keys[j0 + i] : 0u;
         }
       }
 #pragma unroll
-      for (int i = 0; i < kRun; ++i) key[i] = __builtin_bit_cast(uint32_t, p[i]) & kKeyMask;
-      if (j0 + kRun <= v.seg1) {
-#pragma unroll
-        for (int i = 0; i < kRun; i += 4) st16(v.keys + j0 + i, u32x4{key[i], key[i + 1], key[i + 2], key[i + 3]});
-      } else {
-#pragma unroll
-        for (int i = 0; i < kRun; ++i)
-          if (j0 + i < v.seg1) v.keys[j0 + i] = key[i];
-      }
-    } else {
-      if (j0 + kRun <= v.seg1) {
-        const u32x4 w = ld16(v.keys + j0);
-#pragma unroll
-        for (int i = 0; i < kRun; ++i) key[i] = w[i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < kRun; ++i) key[i] = j0 + i < v.seg1 ? v.keys[j0 + i] : 0u;
-      }
+      for (int i = 0; i < RUN; ++i)
+        if (j0 + i < v.seg1 && (key[i] & pmask) == prefix)
+          atomicAdd(&my_hist[(key[i] >> kShift[PASS]) & (kBins[PASS] - 1)], 1u);
     }
-#pragma unroll
-    for (int i = 0; i < kRun; ++i)
-      if (j0 + i < v.seg1 && (key[i] & pmask) == prefix)
-        atomicAdd(&my_hist[(key[i] >> kShift[PASS]) & (kBins[PASS] - 1)], 1u);
-  }
+  };
+  // Pass 1: 16 bytes of keys.  Pass 0: 16 bytes of codes a head (half a block)
+  // where the segment gives every thread that many, fewer in shorter ones, where
+  // the chain of a thread's exponentials is what the launch takes.  The two
+  // passes of 32 lists of 131000 positions: 15.6 and 8.0 us, 18.9 and 11.0 with
+  // one position a thread; pass 0 of 80 lists of 700 positions and 16 heads 9.4 us,
+  // 17.5 with eight.
+  using std::integral_constant;
+  const int n = v.seg1 - v.seg0;
+  if (PASS > 0 || (n > kTopkThreads && n <= 4 * kTopkThreads)) visit(integral_constant<int, 4>{});
+  else if (n > kTopkThreads) visit(integral_constant<int, 8>{});
+  else visit(integral_constant<int, 1>{});
   __syncthreads();
   uint32_t* dst = v.my_part + (int64_t)PASS * kTopkParts * 2048;
   for (int i = t; i < 2048; i += kTopkThreads) {

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (2, 8000, [8000, 7777], 7, 1, 128, [0], 64),                          # 7 heads: 32 blocks
     (2, 5000, [4993, 33], 4, 4, 128, [0, 1, 0, 0], 40),                   # 1 head: 226 blocks
     (130, 300, [(37 * i) % 300 + 1 for i in range(130)], 8, 2, 64, [0, 1], 20),  # whole items per wavefront
+    (5, 4200, [1023, 1024, 1025, 4096, 4097], 2, 1, 64, [0], 50),         # runs of 1 and 4 positions of the selection
     (66, 700, [(53 * i) % 700 + 1 for i in range(66)], 32, 2, 128, [0, 0], 30),  # 16 heads: 14 blocks
 ])
 def test_anchor_score_buffer(B, L, lens, hq, hkv, d, mask, top_k):
