@@ -274,7 +274,8 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
   if ((st = schedule_heads(head_is_streaming, (int)Hkv, &hs))) return st;
   const int gs = (int)(Hq / Hkv);
   const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed, hs.n_ret, hs.n_str);
-  if (ceil_div(T, rows) * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
+  // the limit does not depend on the rows that a call happens to take
+  if (ceil_div(T, dt == AOH_BF16 ? 256 : rows) * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
   const int64_t n_qblocks = ceil_div(std::min(T, n_rows), rows);  // no sequence is longer than all rows
   if (append) {
     if ((st = check_paged(kv_full, hs.n_ret, B))) return st;

@@ -8,8 +8,9 @@ import pytest
 import torch
 
 import synth
-from paper_2608_06849_amd import (PagedCache, RingCache, aoh_kv_append, aoh_prefill, aoh_prefill_append,
+from paper_2608_06849_amd import (AohError, PagedCache, RingCache, aoh_kv_append, aoh_prefill, aoh_prefill_append,
                                   aoh_prefill_chunked, aoh_prefill_varlen)
+from paper_2608_06849_amd.aoh import AOH_ERR_UNSUPPORTED
 from tests.helpers import BF16_MAX_ABS, BF16_MEAN_ABS, bits, to_dtype
 
 pytestmark = pytest.mark.gpu
@@ -157,6 +158,21 @@ def test_grids_of_2_32_work_items(d):
         got.append([out, full.k, full.v, ring.k, ring.v])
     for a, w in zip(*got):
         assert np.array_equal(bits(a), bits(w))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_limit_on_the_bound(d):
+    # blocks of 256 rows x heads x sequences below 2^31 are accepted whatever rows the call takes
+    lens, hq = [1, 130, 64, 200, 7, 128, 129, 3], 32
+    total = sum(lens)
+    g = torch.Generator(device=DEV).manual_seed(d)
+    q, k, v = (torch.randn((total, h, d), dtype=torch.bfloat16, device=DEV, generator=g) for h in (hq, 2, 2))
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device=DEV)
+    got, want = (aoh_prefill_varlen(q, k, v, cu, n, MASK, N_SINK, WINDOW) for n in (1 << 30, max(lens)))
+    assert np.array_equal(bits(got), bits(want))
+    with pytest.raises(AohError) as e:
+        aoh_prefill_varlen(q, k, v, torch.cat([cu, cu[-1:].expand(8)]), 1 << 30, MASK, N_SINK, WINDOW)
+    assert e.value.status == AOH_ERR_UNSUPPORTED
 
 
 def test_dense_batch_of_2_31_work_items():
