@@ -23,7 +23,10 @@ namespace aoh {
 // known.  A chunk that fills a page (or ring block) writes V through the LDS
 // tile as 16-byte vectors, 8 positions of a dimension each.  4 x 4096 tokens, 8
 // KV heads of width 128, half of them streaming: 17.3 us a call, 23.1 with
-// 2-byte stores of V.
+// 2-byte stores of V.  Several positions of a page that is not filled pass
+// through the tile too, so that a dimension's 2-byte stores are contiguous (64 x
+// 16 tokens at odd positions, 8 heads of width 128: 4.5 us, 6.6 without, where
+// a single position is faster straight from the row: 2.5, 3.3).
 template <int D, typename T>
 __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
   constexpr int kVec = 16 / sizeof(T);          // elements per 16-byte vector
@@ -79,15 +82,19 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
     cv_ = reinterpret_cast<T*>(a.pv);
     v_token_major = a.v_token_major;
   } else {
-    const int first = slot_of(p_lo);
-    whole = whole && kept(p_lo) && kept(p_hi - 1) && first % kPage == 0 && slot_of(p_hi - 1) == first + kPage - 1 &&
-            (p_hi <= a.n_sink || p_lo >= max(a.n_sink, end - a.window));
+    int first = 0;
+    whole = whole && kItems >= 256;  // bf16 of width 64 leaves half of the threads idle there
+    if (whole) {
+      first = slot_of(p_lo);
+      whole = kept(p_lo) && kept(p_hi - 1) && first % kPage == 0 && slot_of(p_hi - 1) == first + kPage - 1 &&
+              (p_hi <= a.n_sink || p_lo >= max(a.n_sink, end - a.window));
+    }
     unit0 = ((int64_t)b * a.n_str + rank) * a.ring_blocks + (whole ? first / kPage : 0);
     ck = reinterpret_cast<T*>(a.rk);
     cv_ = reinterpret_cast<T*>(a.rv);
   }
 
-  if (v_token_major || whole) {
+  if (v_token_major || whole || (!streaming && p_hi - p_lo > 1)) {
     T* uk = ck + unit0 * (kPage * D);
     T* uv = cv_ + unit0 * (kPage * D);
 #pragma unroll
@@ -103,6 +110,13 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
     if (v_token_major) return;  // uniform across the workgroup
     __syncthreads();
     // Dimension-major V unit: element (d, r) at uv[d * 16 + r].
+    if (!whole) {  // part of a page
+      for (int e = tid; e < D * kPage; e += 256) {
+        const int d = e / kPage, r = e % kPage, p = lp * kPage + r;
+        if (p >= p_lo && p < p_hi) uv[(int64_t)d * kPage + r] = vtile[r][d];
+      }
+      return;
+    }
     for (int e = tid; e < D * (kPage / kVec); e += 256) {
       const int d = e / (kPage / kVec), r0 = (e % (kPage / kVec)) * kVec;
       T w[kVec];
