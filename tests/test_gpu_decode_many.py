@@ -66,9 +66,11 @@ def test_sequences_without_tokens():
     assert np.isnan(f64(out)[~keep]).all()
     assert_parity(out[torch.from_numpy(keep).to(DEV)], want[keep], torch.bfloat16, "rows with tokens")
     new = torch.zeros((B, Hkv, D), dtype=torch.bfloat16, device=DEV)
-    before = [bits(c) for c in (run.full.k, run.ring.k)]
-    aoh_decode_step(q, new, new, run.full, run.ring, run.mask, torch.zeros_like(lens), 4, 60, workspace=run.ws)
-    assert all(np.array_equal(bits(c), w) for c, w in zip((run.full.k, run.ring.k), before))
+    caches = (run.full.k, run.full.v, run.ring.k, run.ring.v)
+    before = [bits(c) for c in caches]
+    out = aoh_decode_step(q, new, new, run.full, run.ring, run.mask, torch.zeros_like(lens), 4, 60, workspace=run.ws)
+    assert np.isnan(f64(out)).all()
+    assert all(np.array_equal(bits(c), w) for c, w in zip(caches, before))
 
 
 @pytest.mark.parametrize("B,D", [(2, 128), (3, 64), (64, 128), (130, 64), (1030, 64)])
