@@ -201,9 +201,11 @@ constexpr int kManyShortBlocks = 32;
 DecodeKernel decode_kernel(int64_t B, int64_t Hkv, int gs, int D, int64_t blocks, int cu, size_t workspace) {
   const int64_t items = B * Hkv;
   int64_t many = D == 128 ? 128 : 256;
-  if (blocks > kManyShortBlocks) many = D == 128 ? (gs == 1 ? 384 : gs < 4 ? 192 : 128) : (gs == 1 ? 512 : gs < 4 ? 384 : 256);
+  if (blocks > kManyShortBlocks)
+    many = D == 128 ? (gs == 1 ? 384 : gs < 4 ? 192 : 128) : (gs == 1 ? 512 : gs < 4 ? 384 : 256);
   const size_t need = many_rows(cu, gs) * (D + 2) * sizeof(float) + 16 + 8 * cu * sizeof(int32_t);
-  if ((B > kWsMaxBatch || items >= many) && B <= kManyMaxBatch && items * (blocks + 16) < (1ll << 29) && need <= workspace)
+  if ((B > kWsMaxBatch || items >= many) && B <= kManyMaxBatch && items * (blocks + 16) < (1ll << 29) &&
+      need <= workspace)
     return DecodeKernel::kMany;
   return B <= kWsMaxBatch && items * blocks < (1ll << 30) ? DecodeKernel::kWorkSpace : DecodeKernel::kFixed;
 }
@@ -275,7 +277,8 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
   const int gs = (int)(Hq / Hkv);
   const int rows = prefill_rows(dt, (int)D, n_rows, B, T, packed, hs.n_ret, hs.n_str);
   // the limit does not depend on the rows that a call happens to take
-  if (ceil_div(T, dt == AOH_BF16 ? 256 : rows) * Hq * B >= (1ll << 31)) return fail(AOH_ERR_UNSUPPORTED, "grid too large");
+  if (ceil_div(T, dt == AOH_BF16 ? 256 : rows) * Hq * B >= (1ll << 31))
+    return fail(AOH_ERR_UNSUPPORTED, "grid too large");
   const int64_t n_qblocks = ceil_div(std::min(T, n_rows), rows);  // no sequence is longer than all rows
   if (append) {
     if ((st = check_paged(kv_full, hs.n_ret, B))) return st;
@@ -570,11 +573,9 @@ static size_t anchor_ml_bytes(int64_t B, int64_t Hq) { return align256((size_t)(
 static size_t anchor_part_bytes(int64_t B, int64_t Hq) {
   return align256((size_t)(B * Hq * kTopkPasses * kTopkParts * 2048) * sizeof(uint32_t));
 }
-static constexpr size_t kAnchorSpareBytes = 1280;  // unused; the size of the workspace is part of the interface
 static size_t anchor_extra(int64_t B, int64_t Hq, int64_t max_pages) {
   return anchor_codes_bytes(B, Hq, max_pages) + anchor_refs_bytes(B, Hq, max_pages) +
-         anchor_keys_bytes(B, Hq, max_pages) + anchor_ml_bytes(B, Hq) + anchor_part_bytes(B, Hq) +
-         kAnchorSpareBytes;
+         anchor_keys_bytes(B, Hq, max_pages) + anchor_ml_bytes(B, Hq) + anchor_part_bytes(B, Hq);
 }
 
 // H2Share roles of a decode call (Sec. "AoH-Guided Sparse Attention"): plain,

@@ -38,10 +38,11 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 x) { return __builtin_bit_cast
 // The slice is streamed through LDS 64 columns at a time: eight lanes load the
 // 128 bytes of a row, so that an instruction touches whole cache lines, two
 // stages ahead of the MFMAs (28 layers of 32 heads of width 128, d_model 3584:
-// 177 us, 4.6 TB/s; half rows a thread and one stage ahead took 190).  Wave w owns 32-row block w as the A operand and computes the 32x32
-// tiles (w, c) for c >= w; each tile is written with its transpose, so G is
-// exactly symmetric.  The sum over d_model is order-free, so both operands use
-// the same k mapping (k = k0 + 32 * half + 8 * s + j for MFMA step s, element j).
+// 177 us, 4.6 TB/s; half rows a thread and one stage ahead took 190).  Wave w
+// owns 32-row block w as the A operand and computes the 32x32 tiles (w, c) for
+// c >= w; each tile is written with its transpose, so G is exactly symmetric.
+// The sum over d_model is order-free, so both operands use the same k mapping
+// (k = k0 + 32 * half + 8 * s + j for MFMA step s, element j).
 constexpr int kGramRowPad = kGramBK + 8;  // bf16 per LDS row (bank spread)
 
 template <int D>
@@ -177,13 +178,14 @@ __device__ __forceinline__ double sum8(double v) {
 }
 
 // Right-looking Cholesky of G_K = L L^T.  Step k: the owners of row k publish
-// it (by symmetry also column k), every thread scales its row entries by
-// 1 / pivot and updates its elements right of and below the pivot.  An element
-// is final once its column is eliminated, so column k of the lower triangle
-// ends as L[:, k] * L[k][k] in the owners' registers; the scaling and the
-// stores come after the last step (stores inside the loop would be drained at
-// every barrier: 140 us for 112 groups of width 128 that way, 42 this way).  A pivot <= 0 (W_K of lower rank than d_head, up to rounding)
-// zeroes its column, which keeps L L^T equal to G_K on the range of W_K.
+// it (by symmetry also column k), every thread scales its row entries by 1 /
+// pivot and updates its elements right of and below the pivot.  An element is
+// final once its column is eliminated, so column k of the lower triangle ends
+// as L[:, k] * L[k][k] in the owners' registers; the scaling and the stores
+// come after the last step (stores inside the loop would be drained at every
+// barrier: 140 us for 112 groups of width 128 that way, 42 this way).  A pivot
+// <= 0 (W_K of lower rank than d_head, up to rounding) zeroes its column, which
+// keeps L L^T equal to G_K on the range of W_K.
 template <int D>
 __global__ __launch_bounds__(kEigThreads) void chol_kernel(ClassifyArgs a) {
   constexpr int NB = D / 16;

@@ -314,7 +314,6 @@ __device__ __forceinline__ void decode_split_body(const DecodeArgs& a, const Cac
   l_out = l_tot;
 }
 
-
 // Reuse layer of H2Share: one wave per (sequence, paged KV head, split of its
 // borrowed position list).  The same 16x16x32 MFMA structure as the dense
 // body, on gathered tokens: each lane loads the K rows of its two MFMA rows
@@ -450,15 +449,6 @@ __device__ __forceinline__ void decode_sparse_body(const DecodeArgs& a, const Ca
   l_out = l_tot;
 }
 
-// One launch for both cache types: paged-cache items first, ring items last.
-// MODE 0: plain decode; 1: anchor layer (paged items also keep their scores);
-// 2: reuse layer (paged items attend to borrowed positions only); 3: plain
-// decode that first stores the new token at position lens - 1 (fused step).
-// A workgroup holds kSplitWaves consecutive splits of one (sequence, KV
-// head), one per wave; the waves' partials are merged in LDS (log-sum-exp
-// weights, as in the merge pass) and the group writes one partial, so the
-// merge pass reads kSplitWaves times fewer.  Each wave then combines a share
-// of the dimension blocks.
 // The kSplitWaves waves' partial states (acc, m in log2 units, l) merged in
 // LDS with log-sum-exp weights; lane (col, G) holds query head col of the
 // group, and each wave writes a share of the dimension blocks of the merged
@@ -730,24 +720,25 @@ __global__ __launch_bounds__(kSplitWaves * kWave, 2) void decode_ws_kernel(Decod
 
 // ---------------------------------------------------------------------------
 // Split pass for steps of many items (up to kManyMaxBatch sequences): the same
-// work space, in which every item is preceded by kItemCost places without a block: what
-// starting a segment costs a wave (its first loads), in blocks, so that ranges
-// of many short items hold fewer blocks.  Each workgroup takes one contiguous
-// range and each of its waves a consecutive quarter of it.  An item that lies
-// within one wave's quarter is finished and stored by that wave; the pieces of
-// an item that several waves share meet in LDS (at most two a wave: the item
-// its quarter starts in and the one it ends in), and those of several
+// work space, in which every item is preceded by kItemCost places without a
+// block: what starting a segment costs a wave (its first loads), in blocks, so
+// that ranges of many short items hold fewer blocks.  Each workgroup takes one
+// contiguous range and each of its waves a consecutive quarter of it.  An item
+// that lies within one wave's quarter is finished and stored by that wave; the
+// pieces of an item that several waves share meet in LDS (at most two a wave:
+// the item its quarter starts in and the one it ends in), and those of several
 // workgroups in the workspace, for the merge launch, which finds them through
 // ws_items: by workgroup, the item that starts in it and goes on, if any.
 //
 // The ranges of the two rounds are those of decode_ws_kernel.  For few items
-// that kernel's plan, which every wave holds in registers, starts faster (9.5 us
-// a launch against 12 for one sequence of 4093 tokens in ranges of 16 blocks).  For many, its barriers
-// and workspace partials at every item cost more, as do fixed splits of the
-// capacity, of which most are empty when lengths differ: 96 sequences of
-// 200-8000 tokens, 8 KV heads of width 128, capacity 8192: 160 us a step here,
-// 333 with fixed splits; 64 of 200-400 tokens: 28 us here, 51 with the other
-// work-space kernel.  Bound: HBM, 5.4-6 TB/s for full ranges.
+// that kernel's plan, which every wave holds in registers, starts faster (9.5
+// us a launch against 12 for one sequence of 4093 tokens in ranges of 16
+// blocks).  For many, its barriers and workspace partials at every item cost
+// more, as do fixed splits of the capacity, of which most are empty when
+// lengths differ: 96 sequences of 200-8000 tokens, 8 KV heads of width 128,
+// capacity 8192: 160 us a step here, 333 with fixed splits; 64 of 200-400
+// tokens: 28 us here, 51 with the other work-space kernel.  Bound: HBM, 5.4-6
+// TB/s for full ranges.
 constexpr int kItemCost = 4;
 
 struct ManyPlan {

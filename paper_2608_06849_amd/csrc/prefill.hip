@@ -181,10 +181,10 @@ __global__ __launch_bounds__(kPrefillRowsF32) void prefill_f32_kernel(PrefillArg
 //    part of the slower ones' share.
 // Shape of a workgroup of ROWS query rows, 32 a wave: 8 waves in two phase-
 // shifted groups, or 4 waves and two (d_head 128) or three (64) workgroups a
-// CU, which drift apart by themselves.  Loads run kAhead tiles ahead.  A tile's K is last read
-// in its own MFMA phase, its V in the next one: with loads two tiles ahead K
-// needs two slots and V three.  The slots also hold a block's diagonal tiles
-// for the append after the loop (ROWS / kBN of them).
+// CU, which drift apart by themselves.  Loads run kAhead tiles ahead.  A tile's
+// K is last read in its own MFMA phase, its V in the next one: with loads two
+// tiles ahead K needs two slots and V three.  The slots also hold a block's
+// diagonal tiles for the append after the loop (ROWS / kBN of them).
 template <int D, int ROWS>
 struct PPShape {
   static constexpr int kThreads = 2 * ROWS;
@@ -239,11 +239,11 @@ constexpr int kWaitVm0 = 0x0 | (0x7 << 4) | (0xF << 8);
 constexpr int wait_vm(int n) { return n | (0x7 << 4) | (0xF << 8); }  // n < 16
 constexpr int kWaitLgkm0 = 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14);
 
-
 // Work item of a workgroup: query block qb (rows qb * ROWS ..), local query
-// head qh_local of the launch's KV-head list and sequence b.  Dense batches use the XCD-aware order below; packed batches
-// with sequence-major order walk cu_seqlens.  Returns false when the
-// workgroup has no work (past the last sequence's blocks).
+// head qh_local of the launch's KV-head list and sequence b.  Dense batches use
+// the XCD-aware order below; packed batches with sequence-major order walk
+// cu_seqlens.  Returns false when the workgroup has no work (past the last
+// sequence's blocks).
 template <int ROWS>
 __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int wg, int& qb, int& qh_local, int& b) {
   const int n_qh = a.n_kv * a.gs;
@@ -360,7 +360,8 @@ __device__ __forceinline__ void pp_write_tile(const PrefillArgs& a, const uint16
       const int slot = p < a.n_sink ? p : a.n_sink + (p - a.n_sink) % a.window;
       const int64_t unit = ((int64_t)b * a.n_cache + crank) * a.ring_blocks + slot / kPageTokens;
       const int r = slot % kPageTokens;
-      st16(ck + unit * (kPageTokens * D) + r * D + 8 * ch, *reinterpret_cast<const u32x4*>(&tk[PPTile<D>::koff(row, ch)]));
+      st16(ck + unit * (kPageTokens * D) + r * D + 8 * ch,
+           *reinterpret_cast<const u32x4*>(&tk[PPTile<D>::koff(row, ch)]));
       uint16_t* rv = cv + unit * (kPageTokens * D);
       const int vo = PPTile<D>::voff(row, ch);
 #pragma unroll
@@ -839,12 +840,6 @@ __device__ __forceinline__ int pp_grab(uint32_t* q, int n, int x) {
   }
 }
 
-// Both head types of a layer in one launch: workgroups [0, n_ret) take the
-// retrieval items, [ret_pad, ret_pad + n_dyn) the n_str streaming ones
-// through the queues above (ret_pad = n_ret rounded up to the 8 XCDs, so both
-// item spaces keep their XCD-aware order).  The light streaming items are
-// dispatched last and fill the CUs that the causal retrieval items leave
-// idle at the end.
 // One tail item for this workgroup (every thread gets it), or -1: n tail
 // items, n_dyn workgroups of the launch take part.  The last of them to take
 // (or fail to take) an item clears the slot.
@@ -871,8 +866,8 @@ constexpr bool kPPDynamic = D == 128 && ROWS == 256;
 // One head type: workgroups [0, n_static) take items [0, n_static) in the
 // XCD-aware order, the n_dyn others the tail items [n_static, n_static + n_tail).
 template <int D, int ROWS, bool STREAM, bool OUT_F32, bool APPEND>
-__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_kernel(PrefillArgs a, int n_static, int n_tail,
-                                                                            int n_dyn, int slot) {
+__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_kernel(
+    PrefillArgs a, int n_static, int n_tail, int n_dyn, int slot) {
   __shared__ __align__(1024) PPRing<D, ROWS> ring;
   int w = blockIdx.x;
   if constexpr (kPPDynamic<D, ROWS>) {
@@ -892,9 +887,8 @@ __global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void p
 // n_str) take them in order.  The light streaming items are dispatched last
 // and fill the CUs that the causal retrieval items leave idle at the end.
 template <int D, int ROWS, bool OUT_F32, bool APPEND>
-__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_mixed_kernel(PrefillArgs ar, PrefillArgs as,
-                                                                                  int n_ret, int ret_pad, int n_str,
-                                                                                  int n_dyn, int slot) {
+__global__ __launch_bounds__(2 * ROWS, (PPShape<D, ROWS>::kWavesPerSimd)) void prefill_pp_mixed_kernel(
+    PrefillArgs ar, PrefillArgs as, int n_ret, int ret_pad, int n_str, int n_dyn, int slot) {
   __shared__ __align__(1024) PPRing<D, ROWS> ring;
   const int wg = blockIdx.x;
   if (wg < n_ret) {
