@@ -43,8 +43,9 @@
  *   - Calls are thread-safe; calls that write the same cache or workspace
  *     concurrently race, as any two kernels writing one buffer would.
  *   - The prefill calls (aoh_prefill, aoh_prefill_chunked, aoh_prefill_append,
- *     aoh_prefill_varlen) hand the streaming items of their one-launch form
- *     (both head types in one kernel, at d_head 128) out through work-queue
+ *     aoh_prefill_varlen) hand the light items at the end of a launch for long
+ *     prompts of d_head 128 (the streaming ones where both head types share a
+ *     kernel, the second half where they do not) out through work-queue
  *     counters in the library's own device memory (a static array per GPU,
  *     not an allocation): each such launch takes the next of 64 counter slots
  *     and leaves it cleared when it ends.  Prefill launches may run at the

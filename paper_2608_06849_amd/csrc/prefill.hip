@@ -247,6 +247,16 @@ constexpr int kWaitLgkm0 = 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14);
 template <int ROWS>
 __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int wg, int& qb, int& qh_local, int& b) {
   const int n_qh = a.n_kv * a.gs;
+  if constexpr (ROWS != 128) {
+    // Both branches set these again; with them the compiler lays out the 256-row
+    // kernels better (retrieval launch of 32768 tokens 3.145 ms, 3.165 without;
+    // 4 packed prompts of 1000-30000 1% faster).
+    const int per_block = n_qh * a.B;
+    qb = a.n_qblocks - 1 - wg / per_block;
+    const int rem = wg % per_block;
+    qh_local = rem % n_qh;
+    b = rem / n_qh;
+  }
   if (!a.seq_major) {
     int b0 = 0, B = a.B;
     if constexpr (ROWS == 128) {
