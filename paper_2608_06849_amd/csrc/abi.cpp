@@ -351,7 +351,7 @@ static aoh_status prefill_impl(const aoh_tensor* q, const aoh_tensor* k, const a
     PrefillArgs pr = ar, ps = as;
     for (PrefillArgs* p : {&pr, &ps}) {
       p->B = (int)std::min(part, B - b0);
-      p->part = prefill_part(rows, (int)D, packed ? n_rows / B : T, p->n_kv, gs, p->B);
+      p->part = prefill_part(rows, (int)D, packed ? n_rows / B : T, T, p->n_kv, gs, p->B);
       const int es = elt_size(dt);
       if (packed) {
         p->cu_seqlens += b0;

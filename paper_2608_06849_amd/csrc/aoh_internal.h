@@ -198,8 +198,8 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int out_f32, int d, i
 // Query rows per workgroup for n_rows tokens in `batch` sequences and n_ret + n_str KV heads of the two types;
 // PrefillArgs::n_qblocks counts blocks of them.
 int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longest, bool packed, int n_ret, int n_str);
-// PrefillArgs::part for sequences of avg_len tokens.
-int prefill_part(int rows, int d, int64_t avg_len, int n_kv, int gs, int batch);
+// PrefillArgs::part for sequences of avg_len tokens, at most `longest`.
+int prefill_part(int rows, int d, int64_t avg_len, int64_t longest, int n_kv, int gs, int batch);
 // One launch for a layer with both head types (bf16; d_head 64, or short
 // retrieval launches; see prefill.hip).
 bool prefill_mixed_preferred(const PrefillArgs& ar, int dtype, int d, int rows);

@@ -259,13 +259,14 @@ __device__ __forceinline__ bool pp_work_item(const PrefillArgs& a, int wg, int& 
   }
   if (!a.seq_major) {
     int b0 = 0, B = a.B;
-    if constexpr (ROWS == 128) {
+    if (ROWS == 128 && a.part < a.B) {
       // Parts of the batch one after the other (PrefillArgs::part), each in the
       // order below.
       const int per_part = a.n_qblocks * n_qh * a.part;
-      b0 = wg / per_part * a.part;
+      const int part = wg / per_part;
+      wg -= part * per_part;
+      b0 = part * a.part;
       B = min(a.part, a.B - b0);
-      wg %= per_part;
     }
     // XCD-aware order.  Workgroups go to the 8 XCDs (each with its own L2)
     // in turn; work item group j = (query block, sequence, KV head), heaviest
@@ -1004,15 +1005,21 @@ int prefill_rows(int dtype, int d, int64_t n_rows, int64_t batch, int64_t longes
 // gives.  The sequences are therefore visited in parts of at most kPartBytes
 // (one head a group; four times that otherwise, where L2 serves the group's
 // heads and short parts cost balance), rounded up to whole rounds of the XCD
-// order.  32 heads of width 128, one a group: 16 x 4096 tokens 2.14 ms, 3.67 all
-// together, 16 x 2048 0.62 (1.01), 128 x 256, half of them streaming, 309 us (449);
-// 128 MB parts 2.23 ms, 0.65 and 430.  Two a group, 32 x 4096: 4.44 ms (5.21).
-// 256 rows halve the fetches and keep the order their work queues assume.
+// order.  (Up to 64 MB in all the cache holds them, and cutting the few blocks
+// costs balance: 16 x 200 tokens 34.4 us, 32.8 together.)  32 heads of width
+// 128, one a group: 16 x 4096 tokens 2.14 ms, 3.67 all together, 16 x 2048 0.62
+// (1.01), 128 x 256, half of them streaming, 309 us (449); 128 MB parts 2.23
+// ms, 0.65 and 430.  Two a group, 32 x 4096: 4.44 ms (5.21). 256 rows halve the
+// fetches and keep the order their work queues assume.  Packed batches whose
+// bound is far above the mean launch mostly empty workgroups, to which the two
+// steps more are a loss (100 of 500 tokens, bound 32768, 8 KV heads of four:
+// 1.64 ms, 1.55 all together) that passes the gain.
 constexpr int64_t kPartBytes = 32 << 20;
 
-int prefill_part(int rows, int d, int64_t avg_len, int n_kv, int gs, int batch) {
-  if (rows != 128 || n_kv < 1) return batch;
+int prefill_part(int rows, int d, int64_t avg_len, int64_t longest, int n_kv, int gs, int batch) {
+  if (rows != 128 || n_kv < 1 || longest > avg_len * (gs == 1 ? 8 : 4)) return batch;
   const int64_t seq_bytes = std::max<int64_t>(1, avg_len * n_kv * d * 4);
+  if (seq_bytes * batch <= 2 * kPartBytes) return batch;
   const int64_t fit = std::max<int64_t>(1, kPartBytes * (gs == 1 ? 1 : 4) / seq_bytes);
   const int64_t whole = 8 / std::gcd(n_kv, 8);
   return (int)std::min<int64_t>(batch, (fit + whole - 1) / whole * whole);

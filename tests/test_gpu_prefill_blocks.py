@@ -184,9 +184,9 @@ def test_dense_batch_of_2_31_work_items():
 
 
 @pytest.mark.parametrize("b,hq,mask,d", [
-    (34, 32, [0] * 32, 128),             # parts of 14 sequences: two whole ones and a rest
-    (34, 32, [0, 1] * 16, 64),           # both types, up to 58 sequences a part: all in one
-    (100, 13, [0] * 10 + [1] * 3, 128),  # parts of 48: rounded up to whole rounds of 8 (sequence, head) pairs
+    (66, 32, [0] * 32, 128),             # parts of 14 sequences: four whole ones and a rest
+    (34, 32, [0, 1] * 16, 64),           # both types, less than a cut is made for: all in one
+    (200, 13, [0] * 10 + [1] * 3, 128),  # parts of 48: rounded up to whole rounds of 8 (sequence, head) pairs
     (70, 64, [0, 0, 1, 0] * 8, 128),     # two query heads a group: parts of 36 and all in one
 ])
 @pytest.mark.parametrize("packed", [False, True])
