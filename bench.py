@@ -125,10 +125,10 @@ DECODE_SOURCES = ("decode.hip", "aoh_device.h", "aoh_internal.h")
 TRAFFIC = {
     "fetch_factor": 524301.2 / 1048576.0,   # FETCH_SIZE of a 1 GiB copy / 1 GiB
     "write_factor": 1048576.0 / 1048576.0,  # WRITE_SIZE of a 1 GiB copy / 1 GiB
-    "prefill_mixed": {"fetch_kib": 461096.2, "write_kib": 263474.1,
-                      "sources": PREFILL_SOURCES, "source_hash": "5dcbaaa8f4a1a748"},
-    "decode_ws": {"fetch_kib": 1080199.9, "write_kib": 1169.9,
-                  "sources": DECODE_SOURCES, "source_hash": "98d45f439367c23c"},
+    "prefill_mixed": {"fetch_kib": 462558.9, "write_kib": 263395.6,
+                      "sources": PREFILL_SOURCES, "source_hash": "df215c67e08a47a0"},
+    "decode_ws": {"fetch_kib": 1081406.2, "write_kib": 1169.9,
+                  "sources": DECODE_SOURCES, "source_hash": "97176a0d44d1761e"},
 }
 
 
